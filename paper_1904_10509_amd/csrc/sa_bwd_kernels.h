@@ -38,8 +38,7 @@
 // The dq kernel repeats the S and dP products of the dkdv kernel; those two
 // extra products per block are the price of having no reduction across
 // workgroups.
-// fp32 path: the same quantities on the VALU, one thread per row for dq and
-// one thread per column for dk / dv.
+// fp32 path: the same quantities in sa_f32.hip.
 #pragma once
 
 #include <atomic>
@@ -73,6 +72,10 @@ hipError_t bwd_bf16_d64(const AttnArgs& a, const void* q, const void* k, const v
 hipError_t bwd_bf16_d128(const AttnArgs& a, const void* q, const void* k, const void* v, const void* o,
                          const void* dout, const float* lse, void* dq, void* dk, void* dv, const BwdWorkspace& ws,
                          hipStream_t stream, int parts);
+// fp32 backward (sa_f32.hip).
+hipError_t bwd_f32(const AttnArgs& a, const void* q, const void* k, const void* v, const void* o, const void* dout,
+                   const float* lse, void* dq, void* dk, void* dv, const BwdWorkspace& ws, hipStream_t stream,
+                   int parts);
 
 namespace {
 

@@ -12,7 +12,7 @@
 // Each lane owns one query row (r = lane % 16), so the row statistics are
 // per lane plus a two-step exchange over the four lane groups.
 //
-// fp32 path: one thread per query row, same online softmax on the VALU.
+// fp32 path: sa_f32.hip.
 #include "sa_internal.h"
 #include "sa_mask.h"
 #include "sa_mfma.h"
@@ -399,85 +399,6 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     }
 }
 
-// ---------------------------------------------------------------------------
-// fp32, VALU: one thread per query row
-// ---------------------------------------------------------------------------
-// The blocks of row qb a walk visits (see WALK_*), as entries e0 .. e1 of the
-// layout (WALK_DENSE: e is the key block itself).
-__device__ inline void row_entries(const AttnArgs& a, int lay, int qb, int* e0, int* e1) {
-    if (a.walk == WALK_DENSE) {
-        *e0 = 0;
-        *e1 = qb + 1;
-        return;
-    }
-    const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
-    *e0 = a.row_ptr[rp];
-    *e1 = a.row_ptr[rp + 1];
-    if (a.walk == WALK_BAND) *e0 = max(*e0, *e1 - (a.l / a.block + 1));
-}
-
-template <int D>
-__global__ void __launch_bounds__(64)
-fwd_f32_kernel(AttnArgs a, const float* __restrict__ q, const float* __restrict__ k,
-               const float* __restrict__ v, float* __restrict__ o, float* __restrict__ lse) {
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int i = blockIdx.x * 64 + threadIdx.x;
-    if (i >= a.n) return;
-    const int qb = i / a.block;
-    const int lay = head_layout(a, h);
-    const int part = part_of_head(a.mode, h);
-    const int32_t wst = window_start(a, subblock_of_head(a.sub, h));
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
-
-    float qr[D], acc[D];
-    for (int t = 0; t < D; ++t) {
-        qr[t] = q[base + (int64_t)i * a.ss + t];
-        acc[t] = 0.f;
-    }
-    float m = -INFINITY, l = 0.f;
-    int e0, e1;
-    row_entries(a, lay, qb, &e0, &e1);
-    for (int e = e0; e < e1; ++e) {
-        const int kb = a.walk == WALK_DENSE ? e : a.col_idx[e];
-        const bool full = a.walk != WALK_DENSE && a.kind[e] == TILE_FULL;
-        for (int jj = 0; jj < a.block; ++jj) {
-            const int j = kb * a.block + jj;
-            if (!full && !attended(a.pattern, part, a.l, a.c, wst, i - a.qshift, j)) continue;
-            const float* kr = k + base + (int64_t)j * a.ss;
-            float s = 0.f;
-            for (int t = 0; t < D; ++t) s = fmaf(qr[t], kr[t], s);
-            s *= a.scale;
-            if (s > m) {
-                float alpha = expf(m - s);
-                l *= alpha;
-                for (int t = 0; t < D; ++t) acc[t] *= alpha;
-                m = s;
-            }
-            float p = expf(s - m);
-            l += p;
-            const float* vr = v + base + (int64_t)j * a.ss;
-            for (int t = 0; t < D; ++t) acc[t] = fmaf(p, vr[t], acc[t]);
-        }
-    }
-    float* orow = o + base + (int64_t)i * a.ss;
-    float* lrow = lse + stat_index(a, b, h, i);
-    if (a.epilogue == EPI_MERGE) {
-        // combine with the O and LSE of the disjoint part already there
-        const float lse1 = *lrow, lse2 = l > 0.f ? m + logf(l) : -INFINITY;
-        const float mx = fmaxf(lse1, lse2);
-        const float w1 = lse1 == -INFINITY ? 0.f : expf(lse1 - mx);
-        const float w2 = l > 0.f ? expf(m - mx) : 0.f;  // weight of acc
-        const float z = w1 + w2 * l;
-        const float inv = z > 0.f ? 1.f / z : 0.f;
-        for (int t = 0; t < D; ++t) orow[t] = (w1 * orow[t] + w2 * acc[t]) * inv;
-        *lrow = z > 0.f ? mx + logf(z) : -INFINITY;
-        return;
-    }
-    float inv = l > 0.f ? 1.f / l : 0.f;
-    for (int t = 0; t < D; ++t) orow[t] = acc[t] * inv;
-    *lrow = l > 0.f ? m + logf(l) : -INFINITY;
-}
-
 template <int D, int BLK>
 hipError_t launch_bf16(const AttnArgs& a, const void* q, const void* k, const void* v, void* o,
                        float* lse, hipStream_t stream) {
@@ -503,15 +424,6 @@ hipError_t launch_bf16_d(const AttnArgs& a, const void* q, const void* k, const 
     }
 }
 
-template <int D>
-hipError_t launch_f32(const AttnArgs& a, const void* q, const void* k, const void* v, void* o,
-                      float* lse, hipStream_t stream) {
-    dim3 grid((unsigned)((a.n + 63) / 64), (unsigned)a.heads, (unsigned)a.batch);
-    hipLaunchKernelGGL((fwd_f32_kernel<D>), grid, dim3(64), 0, stream, a, (const float*)q,
-                       (const float*)k, (const float*)v, (float*)o, lse);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t fwd_launch(const AttnArgs& a, int dtype, const void* q, const void* k, const void* v,
@@ -523,11 +435,7 @@ hipError_t fwd_launch(const AttnArgs& a, int dtype, const void* q, const void* k
         default: return launch_bf16_d<128>(a, q, k, v, o, lse, stream);
         }
     }
-    switch (a.d) {
-    case 32: return launch_f32<32>(a, q, k, v, o, lse, stream);
-    case 64: return launch_f32<64>(a, q, k, v, o, lse, stream);
-    default: return launch_f32<128>(a, q, k, v, o, lse, stream);
-    }
+    return fwd_f32(a, q, k, v, o, lse, stream);
 }
 
 }  // namespace sa

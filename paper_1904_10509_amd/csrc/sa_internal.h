@@ -147,6 +147,8 @@ __device__ inline MaskParams head_mask_params(const AttnArgs& a, int pattern, in
 // Forward.  q, k, v, o use the strides in `a`; lse is [batch, heads, n].
 hipError_t fwd_launch(const AttnArgs& a, int dtype, const void* q, const void* k, const void* v,
                       void* o, float* lse, hipStream_t stream);
+hipError_t fwd_f32(const AttnArgs& a, const void* q, const void* k, const void* v, void* o, float* lse,
+                   hipStream_t stream);
 
 // Backward workspace: D and the base-2 LSE per row [b, h, n] (fp32), then
 // the work queues and the column order of the dK / dV kernel.

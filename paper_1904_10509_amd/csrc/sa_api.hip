@@ -7,6 +7,7 @@
 #include "sparse_attn.h"
 #include "sa_internal.h"
 #include "sa_mask.h"
+#include "sa_strided.h"
 
 namespace {
 
@@ -123,6 +124,9 @@ sa::AttnArgs make_args(const PatternArgs& p, int32_t batch, int32_t heads, int32
     a.lse_sb = (int64_t)heads * p.n;  // LSE and row statistics: [batch, heads, n]
     a.lse_sh = p.n;
     a.lse_ss = 1;
+    a.off = a.lse_off = 0;
+    a.ws_rows = (int64_t)batch * heads * p.n;
+    a.seq = 0;
     a.row_ptr = row_ptr;
     a.col_idx = col_idx;
     a.kind = kind;
@@ -132,57 +136,141 @@ sa::AttnArgs make_args(const PatternArgs& p, int32_t batch, int32_t heads, int32
     return a;
 }
 
-// Strided pattern, merged heads or A2 alone, bf16: A2 by residue classes
-// (Sec. 5.5, a stride becomes a local window once positions are reordered by
-// their residue mod l).  With l dividing n, position i = m l + r (class r,
-// step m) meets j = m' l + r of its own class only, and A2 \ A1 of the merged
+// Strided A2 by residue classes (Sec. 5.5, a stride becomes a local window once
+// positions are reordered by their residue mod l).  Position i = m l + r (class
+// r, step m) meets j = m' l + r of its own class only, and A2 \ A1 of the merged
 // set is {m' <= m - 2}: dense causal attention inside each class, with the
-// queries' causal limit moved back by two steps (A2 alone: by none).  The
-// classes are strided views of the [b, h, n, d] tensors, so the block kernels
-// walk them unchanged: batch = the b h pairs (stride of one head), heads = the
-// l classes (stride of one row), sequence stride l rows, every block kb <= qb
-// present (no layout), LSE and row statistics read back in row order.  The
-// merged set's band A1 runs first over the caller's layout (only its band
-// blocks: with B dividing l, A2 \ A1 never meets them), and the class kernels
-// then combine their part into its O and LSE (forward) or add it to its
-// gradients (backward).  class_args builds the class view's kernel arguments
-// for class blocks of cb positions (merged: queries shifted by two steps);
-// class_plan picks the class block and returns false where the block path
-// stays: fp32, l not dividing n, n / l not a multiple of 16, batch and head
-// strides that do not merge, or sizes the class grid cannot hold.
-int class_args(int64_t n, int32_t l, int32_t cb, int32_t mode, int32_t batch, int32_t heads, int32_t d,
-               int32_t dtype, const int64_t* strides, float scale, sa::AttnArgs* cls) {
-    if (n % l != 0) return SA_ERR_INVALID;
-    const int64_t M = n / l;  // positions per class
+// queries' causal limit moved back by `shift` = 2 steps (A2 alone: by none).
+// The classes are strided views of the [b, h, n, d] tensors, so the block
+// kernels walk them unchanged: batch = the (b, h) units, heads = the l classes
+// (stride of one row), sequence stride l rows, every block kb <= qb present (no
+// layout), LSE and row statistics in row order.  Where class blocks of cb do
+// not divide every class the sequence length goes along (AttnArgs::seq), and the
+// kernels pad the last block of each class.
+int class_view(int64_t n, int32_t l, int32_t cb, int32_t shift, int64_t units, int64_t unit_stride, int64_t ss,
+               int32_t d, int32_t dtype, float scale, sa::AttnArgs* cls) {
     if (cb != 16 && cb != 32 && cb != 64) return SA_ERR_INVALID;
-    if (M % cb != 0) return SA_ERR_INVALID;
-    if (M / cb > 65535 || (int64_t)batch * heads > 65535) return SA_ERR_UNSUPPORTED;  // grid dimensions
-    if (batch > 1 && strides[0] != (int64_t)heads * strides[1]) return SA_ERR_UNSUPPORTED;  // (b, h) as one index
-    const int64_t cls_strides[3] = {strides[1], strides[2], (int64_t)l * strides[2]};
+    const int64_t M = ((n + l - 1) / l + cb - 1) / cb * cb;  // positions per class, padded
+    if (M / cb > 65535 || units > 65535) return SA_ERR_UNSUPPORTED;  // grid dimensions
+    const int64_t cls_strides[3] = {unit_stride, ss, (int64_t)l * ss};
     PatternArgs c;
     int st = check_pattern(M, cb, (int32_t)M, 0, SA_STRIDED, SA_MODE_A1, &c);
     if (st != SA_OK) return st;
-    st = check_tensor_args(c, batch * heads, l, d, dtype, cls_strides);
+    st = check_tensor_args(c, (int32_t)units, l, d, dtype, cls_strides);
     if (st != SA_OK) return st;
-    *cls = make_args(c, batch * heads, l, d, cls_strides, scale, nullptr, nullptr, nullptr, nullptr, nullptr,
+    *cls = make_args(c, (int32_t)units, l, d, cls_strides, scale, nullptr, nullptr, nullptr, nullptr, nullptr,
                      nullptr);
     cls->walk = sa::WALK_DENSE;
-    cls->qshift = mode == SA_MODE_MERGED ? 2 : 0;
-    cls->lse_sb = n;  // row i = m l + r of pair bh sits at bh n + r + m l
+    cls->qshift = shift;
+    cls->seq = M * l == n ? 0 : (int32_t)n;
+    cls->lse_sb = n;  // row i = m l + r of unit u sits at u n + r + m l
     cls->lse_sh = 1;
     cls->lse_ss = l;
+    cls->ws_rows = units * n;
     return SA_OK;
 }
 
-bool class_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d, int32_t dtype, const int64_t* strides,
-                float scale, sa::AttnArgs* cls) {
+// The class view of a call with the caller's class block (which must divide the
+// classes).
+int class_args(int64_t n, int32_t l, int32_t cb, int32_t mode, int32_t batch, int32_t heads, int32_t d,
+               int32_t dtype, const int64_t* strides, float scale, sa::AttnArgs* cls) {
+    if (n % l != 0) return SA_ERR_INVALID;
+    if (cb != 16 && cb != 32 && cb != 64) return SA_ERR_INVALID;
+    if ((n / l) % cb != 0) return SA_ERR_INVALID;
+    if (batch > 1 && strides[0] != (int64_t)heads * strides[1]) return SA_ERR_UNSUPPORTED;  // (b, h) as one index
+    return class_view(n, l, cb, mode == SA_MODE_MERGED ? 2 : 0, (int64_t)batch * heads, strides[1], strides[2], d,
+                      dtype, scale, cls);
+}
+
+// How a bf16 strided call runs without its layout: the band A1 of the heads that
+// attend it, and the residue classes of the heads that attend A2 (merged heads:
+// the rest of A2, combined with the band's results; alternating heads: the band
+// for the even heads, the classes for the odd ones); or merged heads in one pass.
+struct StridedPlan {
+    bool fused;            // merged heads in one pass (sa_strided.hip; arguments: rows)
+    bool band, classes;
+    bool merge;            // the classes' results join the band's
+    sa::AttnArgs b, c;
+    sa::AttnArgs rows;     // row view of the class heads
+};
+
+// Returns false where the block path over the layout stays: fp32; (batch, head)
+// strides that do not make one index; grids out of range; and the sizes below.
+//
+// Merged heads.  Band and class launches meet in bf16 and need classes that fill
+// their blocks (l | n, n / l a multiple of 16) and a band of whole blocks (B | l).
+// Where those hold, one pass is used for the forward up to l = 128 (n = 12,288, 16
+// heads, l = 128: 49 against 56 us; l = 512: 81 against 70; n = 65,536, 8 heads, l =
+// 256: 190 against 160: its waves read the band's keys for 16 rows each, the band
+// kernel for 64) and never for the backward (137 against 135, l = 256 155 against
+// 139).  Elsewhere the choice is between one pass and the block path, which
+// steps through every block that holds a pair: per multiple of l two blocks of a
+// row, every block when l < B, or one cheap diagonal when B divides l.  One pass
+// wins where those outnumber the band's blocks by kFarToBand (forward + backward,
+// 16 heads of 64, 2.4 times: n = 12,288, l = 111 1,379 -> 203 us; 1.5 to 2: n =
+// 1,024, l = 100 66 -> 47; 1.1: n = 4,096, l = 400 103 -> 113; 0.45: l = 600 107 ->
+// 161; diagonals, n = 3,072, l = 128, d = 128, 8 heads 108 -> 108).
+//
+// A2 alone goes by classes from kMinFarBlocks block steps a row on average (n =
+// 8,192, l = 1,000 114 -> 54 us; n = 512, l = 128 44 -> 42), alternating heads, two
+// launches more, from kMinFarAlternate (n = 3,072, l = 128, d = 128 99 -> 52; n = 768,
+// l = 64 43 -> 50).
+constexpr double kFarToBand = 1.3, kMinFarBlocks = 4.0, kMinFarAlternate = 8.0;
+constexpr int32_t kFusedMinStride = 8, kFusedAlignedMaxStride = 128;
+
+bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d, int32_t dtype,
+                  const int64_t* strides, float scale, bool backward, StridedPlan* s) {
     if (p.pattern != sa::STRIDED || dtype != SA_BF16) return false;
-    if (p.mode != SA_MODE_MERGED && p.mode != SA_MODE_A2) return false;
-    if (p.n % p.l != 0 || (p.mode == SA_MODE_MERGED && p.l % p.block != 0)) return false;
-    const int64_t M = p.n / p.l;
-    const int32_t cb = (M % 64 == 0 && M >= 256) ? 64 : (M % 32 == 0 ? 32 : (M % 16 == 0 ? 16 : 0));
-    if (cb == 0) return false;
-    return class_args(p.n, p.l, cb, p.mode, batch, heads, d, dtype, strides, scale, cls) == SA_OK;
+    const bool alternate = p.mode == SA_MODE_INTERLEAVED;
+    const int64_t M = (p.n + p.l - 1) / p.l;  // positions of the longest class
+    s->fused = false;
+    s->merge = p.mode == SA_MODE_MERGED;
+    s->band = p.mode != SA_MODE_A2;
+    const int32_t class_heads = alternate ? heads / 2 : (p.mode == SA_MODE_A1 ? 0 : heads);
+    s->classes = class_heads > 0 && !(s->merge && M <= 2);
+    PatternArgs pb = p;
+    pb.mode = SA_MODE_A1;
+    pb.n_layouts = 1;
+    // every second head (alternate), from the first or the second
+    auto subset = [&](int32_t count, int32_t first) {
+        const int64_t step = alternate ? 2 : 1;
+        const int64_t st[3] = {strides[0], step * strides[1], strides[2]};
+        sa::AttnArgs a = make_args(pb, batch, count, d, st, scale, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+        a.walk = sa::WALK_BAND;
+        a.lse_sb = (int64_t)heads * p.n;
+        a.lse_sh = step * p.n;
+        a.off = first * strides[1];
+        a.lse_off = first * p.n;
+        a.ws_rows = (int64_t)batch * heads * p.n;
+        return a;
+    };
+    if (s->band) s->b = subset(alternate ? (heads + 1) / 2 : heads, 0);
+    if (!s->classes) return true;
+    const int32_t first = alternate ? 1 : 0;
+    s->rows = subset(class_heads, first);
+    // the block path's steps per multiple of l, a diagonal counted as a third
+    const double steps = p.l % p.block == 0 ? 0.35 : (p.l >= p.block ? 2.0 : (double)p.l / p.block);
+    if (s->merge) {
+        const bool aligned = p.n % p.l == 0 && p.l % p.block == 0 && M % 16 == 0;
+        const bool better = aligned ? !backward && p.l <= kFusedAlignedMaxStride
+                                    : 0.5 * (double)(M - 2) * steps >= kFarToBand * (sa::band_blocks(s->rows) + 1);
+        s->fused = better && p.l >= kFusedMinStride && 64 * (int64_t)p.l * strides[2] < ((int64_t)1 << 32) &&
+                   sa::strided_tiles(s->rows) < (1 << 22);
+        if (s->fused) return true;
+        if (!aligned) return false;
+    } else if (0.5 * (double)M * (p.l % p.block == 0 ? 1.0 : steps) < (alternate ? kMinFarAlternate : kMinFarBlocks)) {
+        return false;
+    }
+    if (batch > 1 && (strides[0] != (int64_t)heads * strides[1] || (alternate && heads % 2 != 0))) return false;
+    const int32_t cb = M >= 256 ? 64 : (M > 16 ? 32 : 16);
+    if (class_view(p.n, p.l, cb, s->merge ? 2 : 0, (int64_t)batch * class_heads, s->rows.sh, strides[2], d, dtype,
+                   scale, &s->c) != SA_OK)
+        return false;
+    s->c.lse_sb = s->rows.lse_sh;
+    s->c.off = s->rows.off;
+    s->c.lse_off = s->rows.lse_off;
+    s->c.ws_rows = s->rows.ws_rows;
+    return true;
 }
 
 // Pattern arguments of a decoding step (no block size: S_pos is enumerated).
@@ -232,7 +320,7 @@ int check_bwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_c, int
               const int32_t* row_idx, const uint8_t* kind_t, int32_t batch, int32_t heads, int32_t d_head,
               int32_t dtype, const void* q, const void* k, const void* v, const void* o, const void* dout,
               const float* lse, const int64_t* strides, float softmax_scale, void* dq, void* dk, void* dv,
-              sa::AttnArgs* a, size_t* need, bool* by_classes, sa::AttnArgs* cls) {
+              sa::AttnArgs* a, size_t* need, bool* planned, StridedPlan* plan) {
     PatternArgs p;
     int st = check_pattern(n, block, stride_l, summary_c, pattern, head_mode, &p);
     if (st != SA_OK) return st;
@@ -247,33 +335,29 @@ int check_bwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_c, int
     *need = sa::bwd_workspace_bytes(batch, heads, n, p.nq, p.n_layouts);
     *a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx, kind, col_ptr, row_idx,
                    kind_t);
-    *by_classes = class_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, cls);
+    *planned = strided_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, true, plan);
     return SA_OK;
 }
 
-// The launches of a validated backward call (see class_plan): the band's
-// backward, then the classes' dQ and dK / dV added to it; A2 alone: the row
-// statistics, then the classes' dQ and dK / dV.
+// The launches of a validated backward call.  By a strided plan: the band's
+// stages first (its row statistics go with its dQ), the row statistics of heads
+// without a band, then the classes' dQ and dK / dV, last and together (short
+// classes run them as one launch).
 // `parts`: the stages to launch (sa::BWD_*), in their order.
-hipError_t launch_bwd(sa::AttnArgs a, bool by_classes, sa::AttnArgs cls, int dtype, const void* q, const void* k,
+hipError_t launch_bwd(const sa::AttnArgs& a, bool planned, StridedPlan& plan, int dtype, const void* q, const void* k,
                       const void* v, const void* o, const void* dout, const float* lse, void* dq, void* dk, void* dv,
                       void* ws, hipStream_t s, int parts = sa::BWD_ALL) {
-    if (!by_classes) return sa::bwd_launch(a, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, parts);
-    // the band's stages first (merged; the row statistics, in row order, go
-    // with the band's dQ), or the row statistics alone (A2: no band)
-    const bool merged = a.mode == sa::MODE_MERGED;
-    if (merged) {
-        a.walk = sa::WALK_BAND;
-        cls.epilogue = sa::EPI_ADD;
-    }
+    if (!planned) return sa::bwd_launch(a, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, parts);
+    if (plan.fused) return sa::strided_bwd(plan.rows, q, k, v, o, dout, lse, dq, dk, dv, ws, s, parts);
     hipError_t e = hipSuccess;
-    // the classes' dQ and dK / dV last and together (short classes run them
-    // as one launch)
-    const int band = merged ? parts : parts & sa::BWD_PRE;
-    if (band) e = sa::bwd_launch(a, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, band);
+    if (plan.band) e = sa::bwd_launch(plan.b, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, parts);
+    if (!plan.classes) return e;
+    if (e == hipSuccess && !plan.merge && (parts & sa::BWD_PRE))
+        e = sa::bwd_launch(plan.rows, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, sa::BWD_PRE);
     const int classes = parts & (sa::BWD_DQ | sa::BWD_DKDV);
+    if (plan.merge) plan.c.epilogue = sa::EPI_ADD;
     if (e == hipSuccess && classes)
-        e = sa::bwd_launch(cls, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, classes);
+        e = sa::bwd_launch(plan.c, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s, classes);
     return e;
 }
 
@@ -382,15 +466,16 @@ int sparse_attn_fwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_
     sa::AttnArgs a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx,
                                kind, nullptr, nullptr, nullptr);
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    sa::AttnArgs cls;
-    if (class_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, &cls)) {
+    StridedPlan plan;
+    if (strided_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, false, &plan)) {
         hipError_t e = hipSuccess;
-        if (p.mode == SA_MODE_MERGED) {  // the band first, then the classes merged into it
-            a.walk = sa::WALK_BAND;
-            e = sa::fwd_launch(a, dtype, q, k, v, o, lse, s);
-            cls.epilogue = sa::EPI_MERGE;
+        if (plan.fused) {
+            e = sa::strided_fwd(plan.rows, q, k, v, o, lse, s);
+            return e == hipSuccess ? SA_OK : SA_ERR_HIP;
         }
-        if (e == hipSuccess) e = sa::fwd_launch(cls, dtype, q, k, v, o, lse, s);
+        if (plan.band) e = sa::fwd_launch(plan.b, dtype, q, k, v, o, lse, s);
+        if (plan.merge) plan.c.epilogue = sa::EPI_MERGE;  // the classes join the band
+        if (e == hipSuccess && plan.classes) e = sa::fwd_launch(plan.c, dtype, q, k, v, o, lse, s);
         return e == hipSuccess ? SA_OK : SA_ERR_HIP;
     }
     hipError_t e = sa::fwd_launch(a, dtype, q, k, v, o, lse, s);
@@ -418,16 +503,17 @@ int sparse_attn_bwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_
                     const void* v, const void* o, const void* dout, const float* lse,
                     const int64_t* strides, float softmax_scale, void* dq, void* dk, void* dv,
                     void* workspace, size_t workspace_bytes, void* stream) {
-    sa::AttnArgs a, cls;
+    sa::AttnArgs a;
+    StridedPlan plan;
     size_t need = 0;
-    bool by_classes = false;
+    bool planned = false;
     const int st = check_bwd(n, block, stride_l, summary_c, pattern, head_mode, row_ptr, col_idx, kind, col_ptr,
                              row_idx, kind_t, batch, heads, d_head, dtype, q, k, v, o, dout, lse, strides,
-                             softmax_scale, dq, dk, dv, &a, &need, &by_classes, &cls);
+                             softmax_scale, dq, dk, dv, &a, &need, &planned, &plan);
     if (st != SA_OK) return st;
     if (workspace_bytes < need) return SA_ERR_BUFFER_TOO_SMALL;
     if (need > 0 && (!workspace || !aligned16(workspace))) return SA_ERR_INVALID;
-    hipError_t e = launch_bwd(a, by_classes, cls, dtype, q, k, v, o, dout, lse, dq, dk, dv, workspace,
+    hipError_t e = launch_bwd(a, planned, plan, dtype, q, k, v, o, dout, lse, dq, dk, dv, workspace,
                               static_cast<hipStream_t>(stream));
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
@@ -440,19 +526,20 @@ int sparse_attn_bwd_stage(int64_t n, int32_t block, int32_t stride_l, int32_t su
                           float softmax_scale, void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes,
                           int32_t stages, void* stream) {
     if (stages < 1 || stages > SA_BWD_ALL_STAGES) return SA_ERR_INVALID;
-    sa::AttnArgs a, cls;
+    sa::AttnArgs a;
+    StridedPlan plan;
     size_t need = 0;
-    bool by_classes = false;
+    bool planned = false;
     const int st = check_bwd(n, block, stride_l, summary_c, pattern, head_mode, row_ptr, col_idx, kind, col_ptr,
                              row_idx, kind_t, batch, heads, d_head, dtype, q, k, v, o, dout, lse, strides,
-                             softmax_scale, dq, dk, dv, &a, &need, &by_classes, &cls);
+                             softmax_scale, dq, dk, dv, &a, &need, &planned, &plan);
     if (st != SA_OK) return st;
     if (workspace_bytes < need) return SA_ERR_BUFFER_TOO_SMALL;
     if (need > 0 && (!workspace || !aligned16(workspace))) return SA_ERR_INVALID;
     // the fp32 path has no separate stages
     const int parts = dtype == SA_BF16 ? stages : sa::BWD_ALL;
     if (dtype != SA_BF16 && stages != SA_BWD_ALL_STAGES) return SA_ERR_UNSUPPORTED;
-    hipError_t e = launch_bwd(a, by_classes, cls, dtype, q, k, v, o, dout, lse, dq, dk, dv, workspace,
+    hipError_t e = launch_bwd(a, planned, plan, dtype, q, k, v, o, dout, lse, dq, dk, dv, workspace,
                               static_cast<hipStream_t>(stream), parts);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
@@ -469,12 +556,13 @@ int sparse_attn_bwd_noalloc(int64_t n, int32_t block, int32_t stride_l, int32_t 
                             int32_t heads, int32_t d_head, int32_t dtype, const void* q, const void* k, const void* v,
                             const void* o, const void* dout, const float* lse, const int64_t* strides,
                             float softmax_scale, void* dq, void* dk, void* dv, void* stream) {
-    sa::AttnArgs a, cls;
+    sa::AttnArgs a;
+    StridedPlan plan;
     size_t need = 0;
-    bool by_classes = false;
+    bool planned = false;
     int st = check_bwd(n, block, stride_l, summary_c, pattern, head_mode, row_ptr, col_idx, kind, col_ptr, row_idx,
                        kind_t, batch, heads, d_head, dtype, q, k, v, o, dout, lse, strides, softmax_scale, dq, dk,
-                       dv, &a, &need, &by_classes, &cls);
+                       dv, &a, &need, &planned, &plan);
     if (st != SA_OK) return st;
     if (need > kScratchBytes) return SA_ERR_BUFFER_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -483,7 +571,7 @@ int sparse_attn_bwd_noalloc(int64_t n, int32_t block, int32_t stride_l, int32_t 
     if (st != SA_OK) return st;
     // the workspace's contents on entry are ignored: the pre kernel writes the
     // row statistics and empties the work counters before anything reads them
-    hipError_t e = launch_bwd(a, by_classes, cls, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s);
+    hipError_t e = launch_bwd(a, planned, plan, dtype, q, k, v, o, dout, lse, dq, dk, dv, ws, s);
     return e == hipSuccess ? SA_OK : SA_ERR_HIP;
 }
 

@@ -322,7 +322,8 @@ bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, 
     // of a row reaches the reduction below)
     if (row >= rows) return;
     const int64_t bh = row / a.n, i = row % a.n;
-    const int64_t off = (bh / a.heads) * a.sb + (bh % a.heads) * a.sh + i * a.ss;
+    const int b = (int)(bh / a.heads), h = (int)(bh % a.heads);
+    const int64_t off = head_base(a, b, h) + i * a.ss, si = stat_index(a, b, h, i);
     float acc = 0.f;
     if constexpr (sizeof(T) == 2) {
 #pragma unroll
@@ -334,8 +335,8 @@ bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, 
         for (int t = 0; t < D; ++t) acc = fmaf(o[off + t], dout[off + t], acc);
     }
     if (g != 0) return;
-    ndelta[row] = -acc;
-    nlse2[row] = -lse[row] * kLog2e;  // an empty row (LSE = -inf) gives +inf; its items are all masked
+    ndelta[si] = -acc;
+    nlse2[si] = -lse[si] * kLog2e;  // an empty row (LSE = -inf) gives +inf; its items are all masked
 }
 
 // ---------------------------------------------------------------------------
@@ -400,7 +401,11 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lay = head_layout(a, h);
     const MaskParams mp = head_mask_params(a, PAT, MODE, h);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
+    // residue classes run as strided A1: only that kernel may meet padding rows
+    constexpr bool kPadded = PAT == STRIDED && MODE == MODE_A1;
+    const int rows = kPadded ? head_rows(a, h) : a.n;
+    if (kPadded && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
     const int row0 = qb * BLK + w * C::RW;
     const int qs0 = qb * BLK - a.qshift;  // first query row of the block as the masks see it
     const float c2 = a.scale_log2;
@@ -415,7 +420,8 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     f32x4 dqacc[C::QBW][C::DB];
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
-        const int i = row0 + 16 * u + r;
+        const bool real = !kPadded || row0 + 16 * u + r < rows;
+        const int i = real ? row0 + 16 * u + r : rows - 1;
 #pragma unroll
         for (int ks = 0; ks < C::KS; ++ks) {
             qf[u][ks] = ld_bf16x8(q + base + (int64_t)i * a.ss + ks * 32 + 8 * g);
@@ -432,7 +438,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                 part += dot_bf16x8(of[u][ks], ld_bf16x8(o + base + (int64_t)i * a.ss + ks * 32 + 8 * g));
             nd = -sum_over_g(part);
             nl2[u] = -lse[si] * kLog2e;  // an empty row (LSE = -inf) gives +inf; its items are all masked
-            if (g == 0) {
+            if (g == 0 && real) {
                 ndelta[si] = nd;
                 nlse2[si] = nl2[u];
             }
@@ -441,17 +447,18 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
             nd = ndelta[si];
         }
         nd4[u] = f32x4{nd, nd, nd, nd};
-        rl[u] = row_lane(i - a.qshift, a.dl);
+        rl[u] = row_lane(row0 + 16 * u + r - a.qshift, a.dl);
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) dqacc[u][db] = zero4();
     }
 
     int e0 = 0, e1 = qb + 1;  // WALK_DENSE: key blocks 0 .. qb
-    if (a.walk != WALK_DENSE) {
+    if (a.walk == WALK_BAND) {
+        e0 = max(0, qb - band_blocks(a));
+    } else if (a.walk == WALK_LAYOUT) {
         const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
         e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
         e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
-        if (a.walk == WALK_BAND) e0 = max(e0, e1 - (a.l / BLK + 1));
     }
     TileLoader<D, BLK, C::NW> ld;
     ld.init(a.ss, w, lane);
@@ -461,6 +468,11 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         const uint32_t kdst = sK_base + stage * kTileBytes, vdst = sV_base + stage * kTileBytes;
         if (!kPairs || s.b < 0) {
             const int64_t kbase = base + (int64_t)s.a * BLK * a.ss;
+            if (kPadded && rows - s.a * BLK < BLK) {
+                ld.issue_rows(k + kbase, kdst, a.ss, rows - s.a * BLK, lane);
+                ld.issue_rows(v + kbase, vdst, a.ss, rows - s.a * BLK, lane);
+                return;
+            }
             ld.issue(k + kbase, kdst);
             ld.issue(v + kbase, vdst);
         } else if constexpr (kPairs) {
@@ -485,7 +497,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     constexpr bool kSumD = decltype(pass)::value == 0;  // the walk that sums D
     // two-stage ring; the next step's blocks are read one step ahead
     RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * BLK),
-                             a.walk == WALK_DENSE};
+                             a.walk != WALK_LAYOUT};
     RowStep cur = steps.next();
     if (cur.a >= 0) load_step(cur, 0);
     two_stage_while([&](auto stage) {
@@ -705,6 +717,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     // this lane holds dQ^T at d = 16 db + 4g + t for query row0 + 16u + r
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
+        if (kPadded && row0 + 16 * u + r >= rows) continue;
         uint16_t* drow = dq + base + (int64_t)(row0 + 16 * u + r) * a.ss;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) {
@@ -942,7 +955,11 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
         const int kb_w = pair && w >= kHalfWaves ? kb + a.l / 64 : kb;  // this wave's key block
         const int qhalf = w / kHalfWaves;  // single half: the 32-query half of each block this wave takes
         const MaskParams mp = head_mask_params(a, PAT, MODE, h);
-        const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+        const int64_t base = head_base(a, b, h);
+        // residue classes run as strided A1: only that kernel may meet padding
+        // rows, or a class that ends before this block (len stays 0: no step)
+        constexpr bool kPadded = PAT == STRIDED && MODE == MODE_A1;
+        const int rows = kPadded ? head_rows(a, h) : a.n;
         // This wave's keys are the 16-key groups w, w + NW, ...: interleaved, so
         // that the waves share the summary columns of the fixed pattern (which
         // sit at the end of a block) and with them the softmax work.  In a
@@ -960,7 +977,7 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
         ColLane cl[C::KBW];
 #pragma unroll
         for (int kbw = 0; kbw < C::KBW; ++kbw) {
-            const int j = key_of(kbw);
+            const int j = kPadded ? min(key_of(kbw), rows - 1) : key_of(kbw);
 #pragma unroll
             for (int ks = 0; ks < C::KS; ++ks) {
                 // In the fixed pattern these rows are read once, and kept out
@@ -976,7 +993,7 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                     vf[kbw][ks] = ld_bf16x8(v + base + (int64_t)j * a.ss + ks * 32 + 8 * g);
                 }
             }
-            cl[kbw] = col_lane(j, a.dl, a.c, mp.w);
+            cl[kbw] = col_lane(key_of(kbw), a.dl, a.c, mp.w);
         }
         // summary keys of this key block (fixed pattern), bit = key offset in the block
         const uint64_t key_summary = PAT == FIXED ? summary_bits(mp, mod_l(a.dl, kb_w * BLK)) & kTileBits : 0ull;
@@ -989,12 +1006,14 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                 dkacc[kbw][db] = zero4();
             }
 
-        int e0 = 0, len = a.nq - kb;  // WALK_DENSE: query blocks kb .. nq - 1
-        if (a.walk != WALK_DENSE) {
+        // WALK_DENSE: query blocks kb .. nq - 1 (to the class's last)
+        int e0 = 0, len = (kPadded ? (rows + BLK - 1) / BLK : a.nq) - kb;
+        if (a.walk == WALK_BAND) {
+            len = min(len, band_blocks(a) + 1);
+        } else if (a.walk == WALK_LAYOUT) {
             const int64_t cp = (int64_t)lay * (a.nq + 1) + kb;
             e0 = __builtin_amdgcn_readfirstlane(col_ptr[cp]);
             len = __builtin_amdgcn_readfirstlane(col_ptr[cp + 1]) - e0;
-            if (a.walk == WALK_BAND) len = min(len, a.l / BLK + 1);
         }
         if (single && ((key_summary >> (32 * (half - 1))) & 0xFFFFFFFFull) == 0ull) {
             // the non-summary half is attended only inside its own l-block:
@@ -1013,16 +1032,22 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
         // blocks at about the same time and share those Q / dO tiles in L2.
         auto query_block = [&](int sidx) {
             const int e = ascend ? sidx : len - 1 - sidx;
-            return a.walk == WALK_DENSE ? kb + e : __builtin_amdgcn_readfirstlane(row_idx[e0 + e]);
+            return a.walk != WALK_LAYOUT ? kb + e : __builtin_amdgcn_readfirstlane(row_idx[e0 + e]);
         };
         auto load_block = [&](int qb, int stage) {
             const int64_t qbase = base + (int64_t)qb * BLK * a.ss;
-            ld.issue(q + qbase, sQ_base + stage * kTileBytes);
-            ld.issue(dout + qbase, sdO_base + stage * kTileBytes);
+            const int n_valid = kPadded ? min(BLK, rows - qb * BLK) : BLK;
+            if (kPadded && n_valid < BLK) {
+                ld.issue_rows(q + qbase, sQ_base + stage * kTileBytes, a.ss, n_valid, lane);
+                ld.issue_rows(dout + qbase, sdO_base + stage * kTileBytes, a.ss, n_valid, lane);
+            } else {
+                ld.issue(q + qbase, sQ_base + stage * kTileBytes);
+                ld.issue(dout + qbase, sdO_base + stage * kTileBytes);
+            }
             const int64_t st0 = stat_index(a, b, h, (int64_t)qb * BLK);
-            if (w == 0) load_row_stats_async(nlse2 + st0, BLK, sL_base + stage * 256u, lane, (uint32_t)a.lse_ss);
+            if (w == 0) load_row_stats_async(nlse2 + st0, n_valid, sL_base + stage * 256u, lane, (uint32_t)a.lse_ss);
             if (w == C::NW - 1)
-                load_row_stats_async(ndelta + st0, BLK, sDl_base + stage * 256u, lane, (uint32_t)a.lse_ss);
+                load_row_stats_async(ndelta + st0, n_valid, sDl_base + stage * 256u, lane, (uint32_t)a.lse_ss);
         };
 
         wait_loads_upto<0>();  // register loads done before the ring starts
@@ -1037,7 +1062,11 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
             const int i0 = qb * BLK - a.qshift;  // first query row of the block as the masks see it
             // a pair's keys are summary keys, attended by every query of a block
             // away from both key blocks' l-blocks
+            // (padding queries at the end of a class are masked)
+            const bool short_block = kPadded && rows - qb * BLK < BLK;
+            const uint64_t valid_bits = short_block ? kTileBits >> (BLK - (rows - qb * BLK)) : kTileBits;
             const bool masked =
+                short_block ? true :
                 pair ? !far_block(PAT, a.dl, i0, (kb + a.l / 64) * BLK, BLK)
                      : !block_full32(PAT, mp.part, a.dl, a.c, mp.w, i0, i0 + BLK - 1, kb * BLK, kb * BLK + BLK - 1);
             wait_loads_upto<0>();
@@ -1119,7 +1148,7 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                     } else {
 #pragma unroll
                         for (int kbw = 0; kbw < C::KBW; ++kbw)
-                            bits[kbw] = (col_mask(mp, cl[kbw], i0, i0_mod) & kTileBits) >> (4 * g);
+                            bits[kbw] = (col_mask(mp, cl[kbw], i0, i0_mod) & valid_bits) >> (4 * g);
                     }
                     if (!(PAT == FIXED && far && mp.part != PART_A1)) {
 #pragma unroll
@@ -1319,6 +1348,7 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
         for (int kbw = 0; kbw < C::KBW; ++kbw) {
             if (single && qhalf == 1) break;  // written by the wave of the other query half
             const int j = key_of(kbw);
+            if (kPadded && j >= rows) continue;
             uint16_t* dvrow = dv + base + (int64_t)j * a.ss;
             uint16_t* dkrow = dk + base + (int64_t)j * a.ss;
 #pragma unroll
@@ -1444,7 +1474,7 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
         // grid stays 2% faster).  Under CLAIM_XCD_SERPENTINE such a grid is
         // the first round alone: the columns of a class unit take consecutive
         // places on one XCD.
-        const bool per_column = (a.walk == WALK_BAND && a.l / BLK + 1 >= 8) || (a.walk == WALK_DENSE && a.nq >= 8);
+        const bool per_column = (a.walk == WALK_BAND && band_blocks(a) + 1 >= 8) || (a.walk == WALK_DENSE && a.nq >= 8);
         const unsigned qgrid = (unsigned)(slots > 0 && slots < items && !per_column
                                               ? slots
                                               : (items < (1ll << 31) ? items : (1ll << 31) - 1));
@@ -1474,16 +1504,18 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
         AttnArgs aq = ak;
         aq.row_stats = (parts & BWD_PRE) && (parts & BWD_DQ) &&
                        (int64_t)a.heads * a.nq * a.batch >= layout_count(a.mode, a.sub);
+        // (a walk without a layout takes its columns in order: no schedule)
+        unsigned long long* const sched = a.walk == WALK_LAYOUT ? ws.queue : nullptr;
         if ((parts & BWD_PRE) && !aq.row_stats)
             hipLaunchKernelGGL((bwd_pre_kernel<D, uint16_t>), dim3((unsigned)pre_groups), dim3(256), 0, stream, ak,
-                               (const uint16_t*)o, (const uint16_t*)dout, lse, ndelta, nlse2, ws.queue, ws.items,
+                               (const uint16_t*)o, (const uint16_t*)dout, lse, ndelta, nlse2, sched, ws.items,
                                ws.order);
         if (parts & BWD_DQ) (void)with_full_body<PAT>(a, [&](auto fb) {
             auto dq_kernel = [&](auto sp) {
                 hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value>),
                                    grid, dim3(DqCfg<D, BLK, PAT>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
                                    (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
-                                   nlse2, ndelta, (uint16_t*)dq, (const uint16_t*)o, lse, ws.queue, ws.items,
+                                   nlse2, ndelta, (uint16_t*)dq, (const uint16_t*)o, lse, sched, ws.items,
                                    ws.order);
             };
             if constexpr (PAT == FIXED) {
@@ -1516,8 +1548,9 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
 // ---------------------------------------------------------------------------
 // In the class view of a strided call each (batch x head, class) unit is
 // dense causal attention over M positions with the causal limit moved back
-// a.qshift steps.  Where M <= 128 (a multiple of 32), one workgroup of M / 16
-// waves takes a unit whole: its Q, K, V, dO and row statistics go into LDS
+// a.qshift steps.  Where M <= 128, one workgroup takes a unit whole, M / 16
+// waves with M rounded up to a multiple of 32 (the padding rows repeat the last
+// one, are masked and are not written): its Q, K, V, dO and row statistics go into LDS
 // once, and
 //   phase 1: wave w takes keys 16 w .. 16 w + 15 and walks the 32-query chunks
 //     that attend them, forming S and dP once per pair: dV and dK accumulate
@@ -1556,7 +1589,8 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
     const int h = blockIdx.x, b = blockIdx.z;  // class, batch x head
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
+    const int rows = head_rows(a, h);  // of M; padding rows repeat the last one and are masked
     const int shift = a.qshift;
     const float c2 = a.scale_log2;
 
@@ -1571,15 +1605,15 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
         const int win = w + C::NW * kk;
         const int oe = 512 * win + 8 * lane;  // element offset of this lane's slot
         const int row = oe / D, chunk = ((oe % D) / 8) ^ Swz<D>::perm(row);
-        const uint32_t off = (uint32_t)(((int64_t)row * a.ss + 8 * chunk) * 2);
+        const uint32_t off = (uint32_t)(((int64_t)min(row, rows - 1) * a.ss + 8 * chunk) * 2);
         dma_b128(uniform_ptr(q + base), off, lds_addr(sQ) + 1024 * win);
         dma_b128(uniform_ptr(k + base), off, lds_addr(sK) + 1024 * win);
         dma_b128(uniform_ptr(v + base), off, lds_addr(sV) + 1024 * win);
         dma_b128(uniform_ptr(dout + base), off, lds_addr(sO) + 1024 * win);
     }
     if (64 * w < M) {
-        const int m0 = 64 * w, nv = M - m0 < 64 ? M - m0 : 64;
-        const int64_t st0 = stat_index(a, b, h, m0);
+        const int m0 = 64 * w, nv = max(1, min(64, rows - m0));
+        const int64_t st0 = stat_index(a, b, h, min(m0, rows - 1));
         load_row_stats_async(nlse2 + st0, nv, lds_addr(sL) + 4 * m0, lane, (uint32_t)a.lse_ss);
         load_row_stats_async(ndelta + st0, nv, lds_addr(sD) + 4 * m0, lane, (uint32_t)a.lse_ss);
     }
@@ -1628,7 +1662,7 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int i = 16 * qblk + 4 * g + t;  // query; pair (i, j) attended when j <= i - shift
-                const float pv = j <= i - shift ? exp2_fast(fmaf(sacc[t], c2, nl[t])) : 0.f;
+                const float pv = j <= i - shift && i < rows ? exp2_fast(fmaf(sacc[t], c2, nl[t])) : 0.f;
                 p[hq][t] = pv;
                 ds[hq][t] = pv * dpacc[t];
             }
@@ -1652,7 +1686,7 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
         *reinterpret_cast<uint2*>(&sST[j * C::MP + 32 * qc + 16 + 4 * g]) = pack_bf16x4_bits(ds[1]);
     }
     // this lane holds dV^T / dK^T at d = 16 db + 4 g + t for key j
-    {
+    if (j < rows) {
         uint16_t* dvrow = dv + base + (int64_t)j * a.ss;
         uint16_t* dkrow = dk + base + (int64_t)j * a.ss;
 #pragma unroll
@@ -1690,6 +1724,7 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
             dqacc[db] = mfma_16x16x32(kT[db & 1], dsb, dqacc[db]);
         }
     }
+    if (q0 + r >= rows) return;
     uint16_t* drow = dq + base + (int64_t)(q0 + r) * a.ss;
 #pragma unroll
     for (int db = 0; db < C::DB; ++db) {
@@ -1706,8 +1741,8 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
 template <int D>
 inline bool class_bwd_fits(const AttnArgs& a) {
     if (a.walk != WALK_DENSE || a.pattern != STRIDED || a.mode != MODE_A1) return false;
-    const int M = a.n;
-    if (M % 32 != 0 || M > 128 || (D == 128 && M > 96)) return false;  // 4 M D + M (M + 8) bf16 within 160 KiB
+    const int M = (a.n + 31) / 32 * 32;
+    if (M > 128 || (D == 128 && M > 96)) return false;  // 4 M D + M (M + 8) bf16 within 160 KiB
     return ((int64_t)(M - 1) * a.ss + D) * 2 < ((int64_t)1 << 32) && a.lse_ss * 64 < ((int64_t)1 << 30);
 }
 
@@ -1730,7 +1765,7 @@ hipError_t launch_bwd_bf16_d(const AttnArgs& a, const void* q, const void* k, co
         if (parts & BWD_PRE)
             e = launch_bwd_bf16_d<D>(a, q, k, v, o, dout, lse, dq, dk, dv, ws, stream, BWD_PRE);
         if (e != hipSuccess) return e;
-        switch (a.n) {
+        switch ((a.n + 31) / 32 * 32) {
         case 32: return launch_class_bwd<D, 32>(a, q, k, v, dout, dq, dk, dv, ws, stream);
         case 64: return launch_class_bwd<D, 64>(a, q, k, v, dout, dq, dk, dv, ws, stream);
         case 96: return launch_class_bwd<D, 96>(a, q, k, v, dout, dq, dk, dv, ws, stream);

@@ -147,7 +147,7 @@ struct TileWalk {
         mp = m;
         dl = a.dl;
         idx = index;
-        dense = a.walk == WALK_DENSE;
+        dense = a.walk != WALK_LAYOUT;
         block = a.block;
         groups = block / 16;
         step = kF32Waves / groups;
@@ -238,22 +238,20 @@ __device__ inline void for_tiles(Next&& next, const float* pa, const float* pb, 
 
 // Entries of row block qb and column block kb a walk visits (see WALK_*).
 __device__ inline void row_entries(const AttnArgs& a, const int32_t* row_ptr, int lay, int qb, int* e0, int* e1) {
-    *e0 = 0;
+    *e0 = a.walk == WALK_BAND ? max(0, qb - band_blocks(a)) : 0;
     *e1 = qb + 1;
-    if (a.walk == WALK_DENSE) return;
+    if (a.walk != WALK_LAYOUT) return;
     const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
     *e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
     *e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
-    if (a.walk == WALK_BAND) *e0 = max(*e0, *e1 - (a.l / a.block + 1));
 }
 __device__ inline void col_entries(const AttnArgs& a, const int32_t* col_ptr, int lay, int kb, int* e0, int* e1) {
     *e0 = kb;
-    *e1 = a.nq;
-    if (a.walk == WALK_DENSE) return;
+    *e1 = a.walk == WALK_BAND ? min(a.nq, kb + band_blocks(a) + 1) : a.nq;
+    if (a.walk != WALK_LAYOUT) return;
     const int64_t cp = (int64_t)lay * (a.nq + 1) + kb;
     *e0 = __builtin_amdgcn_readfirstlane(col_ptr[cp]);
     *e1 = __builtin_amdgcn_readfirstlane(col_ptr[cp + 1]);
-    if (a.walk == WALK_BAND) *e1 = min(*e1, *e0 + a.l / a.block + 1);
 }
 
 // Forward.  grid: (16-row groups, heads, batch), longest rows first.
@@ -269,7 +267,7 @@ fwd_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* _
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const MaskParams mp = head_mask_params(a, a.pattern, a.mode, h);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
     for (int rg = a.n / 16 - 1 - (int)blockIdx.x; rg >= 0; rg -= (int)gridDim.x) {
         const int row0 = 16 * rg, i0 = row0 - a.qshift;
         const RowLane rl = row_lane(i0 + r, a.dl);
@@ -380,7 +378,7 @@ bwd_dq_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const MaskParams mp = head_mask_params(a, a.pattern, a.mode, h);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
     for (int rg = a.n / 16 - 1 - (int)blockIdx.x; rg >= 0; rg -= (int)gridDim.x) {
         const int row0 = 16 * rg, i0 = row0 - a.qshift;
         const RowLane rl = row_lane(i0 + r, a.dl);
@@ -448,7 +446,7 @@ bwd_dkdv_f32_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int32
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const MaskParams mp = head_mask_params(a, a.pattern, a.mode, h);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
     for (int kg = (int)blockIdx.x; kg < a.n / 16; kg += (int)gridDim.x) {
         const int j0 = 16 * kg;
         const ColLane cl = col_lane(j0 + r, a.dl, a.c, mp.w);

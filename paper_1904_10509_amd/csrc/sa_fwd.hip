@@ -70,7 +70,11 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lay = head_layout(a, h);
     const MaskParams mp = head_mask_params(a, PAT, MODE, h);
-    const int64_t base = (int64_t)b * a.sb + (int64_t)h * a.sh;
+    const int64_t base = head_base(a, b, h);
+    // residue classes run as strided A1: only that kernel may meet padding rows
+    constexpr bool kPadded = PAT == STRIDED && MODE == MODE_A1;
+    const int rows = kPadded ? head_rows(a, h) : a.n;
+    if (kPadded && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
     const int row0 = qb * BLK + w * C::RW;  // first query row of this wave
     const int qs0 = qb * BLK - a.qshift;    // first query row of the block as the masks see it
 
@@ -80,9 +84,9 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     RowLane rl[C::QBW];
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
+        const int i = kPadded ? min(row0 + 16 * u + r, rows - 1) : row0 + 16 * u + r;
 #pragma unroll
-        for (int ks = 0; ks < C::KS; ++ks)
-            qf[u][ks] = ld_bf16x8(q + base + (int64_t)(row0 + 16 * u + r) * a.ss + ks * 32 + 8 * g);
+        for (int ks = 0; ks < C::KS; ++ks) qf[u][ks] = ld_bf16x8(q + base + (int64_t)i * a.ss + ks * 32 + 8 * g);
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) oacc[u][db] = zero4();
         m_run[u] = -INFINITY;
@@ -91,11 +95,12 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     }
 
     int e0 = 0, e1 = qb + 1;  // WALK_DENSE: key blocks 0 .. qb
-    if (a.walk != WALK_DENSE) {
+    if (a.walk == WALK_BAND) {
+        e0 = max(0, qb - band_blocks(a));
+    } else if (a.walk == WALK_LAYOUT) {
         const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
         e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
         e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
-        if (a.walk == WALK_BAND) e0 = max(e0, e1 - (a.l / BLK + 1));
     }
     TileLoader<D, BLK, C::NW> ld;
     ld.init(a.ss, w, lane);
@@ -105,6 +110,11 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
         const uint32_t kdst = sK_base + stage * kTileBytes, vdst = sV_base + stage * kTileBytes;
         if (!kPairs || s.b < 0) {
             const int64_t kbase = base + (int64_t)s.a * BLK * a.ss;
+            if (kPadded && rows - s.a * BLK < BLK) {
+                ld.issue_rows(k + kbase, kdst, a.ss, rows - s.a * BLK, lane);
+                ld.issue_rows(v + kbase, vdst, a.ss, rows - s.a * BLK, lane);
+                return;
+            }
             ld.issue(k + kbase, kdst);
             ld.issue(v + kbase, vdst);
         } else if constexpr (kPairs) {
@@ -126,7 +136,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     // two-stage ring; the next step's blocks are read one step ahead (scalar
     // loads, off the vector-memory counter the ring waits on)
     RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * BLK),
-                             a.walk == WALK_DENSE};
+                             a.walk != WALK_LAYOUT};
     // strided blocks away from the band are single diagonals (see the step)
     const bool diag_far = PAT == STRIDED && mp.part != PART_A1 && a.l % BLK == 0;
     RowStep cur = steps.next();
@@ -366,6 +376,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     for (int u = 0; u < C::QBW; ++u) {
         const int i = row0 + 16 * u + r;
         const float l_tot = sum_over_g(l_run[u]);
+        if (kPadded && i >= rows) continue;
         uint16_t* orow = o + base + (int64_t)i * a.ss;
         float* lrow = lse + stat_index(a, b, h, i);
         if (a.epilogue == EPI_MERGE) {

@@ -54,10 +54,9 @@ enum { CLAIM_QUEUES = 0, CLAIM_ROUND_ROBIN = 1, CLAIM_SERPENTINE = 2, CLAIM_XCD_
 
 // Which blocks a kernel walks:
 //   WALK_LAYOUT  the present blocks of the layout;
-//   WALK_BAND    of a strided layout with l a multiple of B, only the blocks of
-//                the band A1 = {i - l .. i}: the last l / B + 1 entries of a
-//                row, the first l / B + 1 of a column (they hold no other
-//                pair of the merged set);
+//   WALK_BAND    the blocks of the strided band A1 = {i - l .. i}, without a
+//                layout: ceil(l / B) blocks before the diagonal one in a row,
+//                after it in a column;
 //   WALK_DENSE   every block kb <= qb, without a layout (dense causal).
 enum { WALK_LAYOUT = 0, WALK_BAND = 1, WALK_DENSE = 2 };
 
@@ -89,6 +88,10 @@ struct AttnArgs {
     int32_t qshift;        // masks see query i as i - qshift (a causal limit j <= i - qshift)
     int32_t epilogue;      // EPI_*
     int64_t lse_sb, lse_sh, lse_ss;  // element strides of LSE and the row statistics (batch, head, row)
+    int64_t off, lse_off;  // first element of the tensors and of LSE / the row statistics (a subset of the heads)
+    int64_t ws_rows;       // rows of the whole call: the size of each row statistic in the workspace
+    int32_t seq;           // residue classes: positions of the whole sequence (class h of l has
+                           // ceil((seq - h) / l) of them, the rest of its last block is padding); else 0
     const int32_t* row_ptr;
     const int32_t* col_idx;
     const uint8_t* kind;
@@ -119,10 +122,25 @@ __device__ inline GridItem row_grid_item(const AttnArgs& a) {
     return {(int)blockIdx.x, a.nq - 1 - (int)blockIdx.y, (int)blockIdx.z};
 }
 
+// First element of (batch b, head h) in the tensors.
+__host__ __device__ inline int64_t head_base(const AttnArgs& a, int b, int h) {
+    return a.off + (int64_t)b * a.sb + (int64_t)h * a.sh;
+}
+
 // Index of row i of (batch b, head h) in LSE and the backward's row statistics.
 __host__ __device__ inline int64_t stat_index(const AttnArgs& a, int b, int h, int64_t i) {
-    return (int64_t)b * a.lse_sb + (int64_t)h * a.lse_sh + i * a.lse_ss;
+    return a.lse_off + (int64_t)b * a.lse_sb + (int64_t)h * a.lse_sh + i * a.lse_ss;
 }
+
+// Rows of head h: in a residue-class view (whose heads are the l classes)
+// class h's positions, else n.  Padding rows beyond them are read as the last
+// row, masked where they are queries of a column, and never written.
+__host__ __device__ inline int head_rows(const AttnArgs& a, int h) {
+    return a.seq > 0 ? (a.seq - 1 - h) / a.heads + 1 : a.n;
+}
+
+// Blocks before (row) or after (column) the diagonal one in the strided band.
+__host__ __device__ inline int band_blocks(const AttnArgs& a) { return (a.l - 1) / a.block + 1; }
 
 // Layout that head h reads.
 __host__ __device__ inline int head_layout(const AttnArgs& a, int h) { return layout_of_head(a.mode, a.sub, h); }
@@ -149,6 +167,12 @@ hipError_t fwd_launch(const AttnArgs& a, int dtype, const void* q, const void* k
                       void* o, float* lse, hipStream_t stream);
 hipError_t fwd_f32(const AttnArgs& a, const void* q, const void* k, const void* v, void* o, float* lse,
                    hipStream_t stream);
+
+// Strided merged heads in one pass (bf16; sa_strided.hip).
+hipError_t strided_fwd(const AttnArgs& a, const void* q, const void* k, const void* v, void* o, float* lse,
+                       hipStream_t stream);
+hipError_t strided_bwd(const AttnArgs& a, const void* q, const void* k, const void* v, const void* o, const void* dout,
+                       const float* lse, void* dq, void* dk, void* dv, void* workspace, hipStream_t stream, int parts);
 
 // Backward workspace: D and the base-2 LSE per row [b, h, n] (fp32), then
 // the work queues and the column order of the dK / dV kernel.

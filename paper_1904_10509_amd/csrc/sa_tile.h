@@ -110,6 +110,19 @@ struct TileLoader {
 #pragma unroll
         for (int kk = 0; kk < PER; ++kk) dma_b128(s, off[kk], base + 1024 * (w + NW * kk));
     }
+    // The same for a tile of which only the first n_valid (>= 1) rows exist: the
+    // others are filled with the last one.
+    __device__ void issue_rows(const uint16_t* src, uint32_t base, int64_t ss, int n_valid, int lane) const {
+        const void* s = uniform_ptr(src);
+#pragma unroll
+        for (int kk = 0; kk < PER; ++kk) {
+            const int win = w + NW * kk;
+            const int oe = 512 * win + 8 * lane;
+            const int row = oe / D, chunk = ((oe % D) / 8) ^ Swz<D>::perm(row);
+            const int from = row < n_valid ? row : n_valid - 1;
+            dma_b128(s, (uint32_t)((from * ss + 8 * chunk) * 2), base + 1024 * win);
+        }
+    }
     // One tile made of two half tiles: rows 0 .. BLK/2-1 from src_lo and rows
     // BLK/2 .. BLK-1 from src_hi, each pointer being where tile row 0 would
     // sit (so tile row R reads row R past its pointer).  A 1 KiB window never

@@ -196,11 +196,13 @@ __device__ void build_schedule(const AttnArgs& a, int g, unsigned long long* que
     __syncthreads();
     const int G = group_blocks(a);
     // a group's class follows the sum of its members' walks (a split block's
-    // short half walks at most the l-block's blocks)
+    // short half walks at most the l-block's blocks); -1: no members.  A group
+    // whose members' columns are all empty (A2 alone, a last l-block that ends
+    // before its summary window) is an item too: its gradients are zero.
     auto group_len = [&](int kb0) {
-        int total = 0;
+        int total = -1;
         for (int kb = kb0; kb < kb0 + G && kb < a.nq; ++kb)
-            if (group_member(a, g, kb, cp) >= 0) total += min(cp[kb + 1] - cp[kb], G);
+            if (group_member(a, g, kb, cp) >= 0) total = max(total, 0) + min(cp[kb + 1] - cp[kb], G);
         return total;
     };
     // (the counting pass takes the same decisions as the placing pass below)
@@ -215,7 +217,7 @@ __device__ void build_schedule(const AttnArgs& a, int g, unsigned long long* que
         if (!G && split) atomicAdd(&cls_pos[lower_cls], 1);
         if (G && kb % G == 0) {
             const int total = group_len(kb);
-            if (total > 0) atomicAdd(&cls_pos[cls_of(total)], 1);
+            if (total >= 0) atomicAdd(&cls_pos[cls_of(total)], 1);
         }
     }
     __syncthreads();
@@ -262,7 +264,7 @@ __device__ void build_schedule(const AttnArgs& a, int g, unsigned long long* que
                 }
                 if (G && kb % G == 0) {
                     const int total = group_len(kb);
-                    if (total > 0) {
+                    if (total >= 0) {
                         code[2] = item_code(kb, kGroupKind);
                         cls[2] = cls_of(total);
                     }

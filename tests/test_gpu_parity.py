@@ -150,6 +150,10 @@ SMALL_CASES = [
     (S, MG, 4096, 32, 32, 0, 64, torch.bfloat16, 1, 2),
     (S, A2, 4096, 32, 32, 0, 128, torch.bfloat16, 1, 1),
     (S, A2, 2048, 32, 32, 0, 32, torch.bfloat16, 2, 2),
+    # A2 alone, a last l-block that ends before its summary window: none of its
+    # keys is attended, and their gradients are zeros
+    (F, A2, 832, 64, 256, 32, 64, torch.bfloat16, 1, 2),
+    (P, IL, 704, 64, 128, 32, 64, torch.bfloat16, 1, 4),
     # few summary keys per row (c = 1, 2), A2 alone, many heads: the summary
     # columns sum hundreds of large weights, so the dV / dK products take P and
     # dS in two bf16 parts (shared window and a subblock per head; B = 64 with

@@ -350,11 +350,12 @@ bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, 
 // and each K / V operand read from LDS then serves 32 rows (16 rows at three
 // waves per SIMD made the fixed backward at n = 65,536 slower: 2.30 against
 // 2.24 ms).
-template <int D, int BLK, int PAT>
+template <int D, int BLK, int PAT, bool WIDE = false>
 struct DqCfg {
-    static constexpr int RW = BLK < 32 || PAT == STRIDED ? 16 : 32;  // query rows per wave
+    static constexpr int RW = !WIDE && (BLK < 32 || PAT == STRIDED) ? 16 : 32;  // query rows per wave
+    static constexpr int QROWS = WIDE ? 2 * BLK : BLK;  // query rows per workgroup
     static constexpr int QBW = RW / 16;
-    static constexpr int NW = BLK / RW;
+    static constexpr int NW = QROWS / RW;
     static constexpr int NT = NW * 64;
     static constexpr int KS = D / 32;
     static constexpr int KB = BLK / 16;
@@ -376,9 +377,9 @@ struct DqCfg {
 // the dK / dV kernel; its first layout_count workgroups build the dK / dV
 // schedule.  The launcher sets it when the grid covers every row and at least
 // that many workgroups, and then launches no pre kernel.
-template <int D, int BLK, int PAT, int MODE, bool FULL_BODY, bool SPLIT>
-__global__ void __launch_bounds__((DqCfg<D, BLK, PAT>::NT))
-    __attribute__((amdgpu_waves_per_eu(DqCfg<D, BLK, PAT>::WAVES_PER_EU)))
+template <int D, int BLK, int PAT, int MODE, bool FULL_BODY, bool SPLIT, bool WIDE>
+__global__ void __launch_bounds__((DqCfg<D, BLK, PAT, WIDE>::NT))
+    __attribute__((amdgpu_waves_per_eu(DqCfg<D, BLK, PAT, WIDE>::WAVES_PER_EU)))
 bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                    const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -386,7 +387,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                    uint16_t* __restrict__ dq, const uint16_t* __restrict__ o, const float* __restrict__ lse,
                    unsigned long long* __restrict__ queue, int32_t* __restrict__ items,
                    int32_t* __restrict__ order) {
-    using C = DqCfg<D, BLK, PAT>;
+    using C = DqCfg<D, BLK, PAT, WIDE>;
     if (a.row_stats && queue) {  // uniform over the workgroup
         const int64_t wg = blockIdx.x + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
         if (wg < layout_count(a.mode, a.sub)) build_schedule(a, (int)wg, queue, items, order);
@@ -407,9 +408,12 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     // residue classes run as strided A1: only that kernel may meet padding rows
     constexpr bool kPadded = PAT == STRIDED && MODE == MODE_A1;
     const int rows = kPadded ? head_rows(a, h) : a.n;
-    if (kPadded && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
-    const int row0 = qb * BLK + w * C::RW;
-    const int qs0 = qb * BLK - a.qshift;  // first query row of the block as the masks see it
+    if (kPadded && !WIDE && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
+    const int row0 = qb * C::QROWS + w * C::RW;
+    // the query rows whose masks decide how a block is treated: the block's, or
+    // (wide) the wave's own
+    const int qs0 = (WIDE ? row0 : qb * BLK) - a.qshift, qs1 = qs0 + (WIDE ? C::RW : BLK) - 1;
+    const int qlast = WIDE ? min(2 * qb + 1, a.nq - 1) : qb;  // last query block (its row holds the others')
     const float c2 = a.scale_log2;
     constexpr uint64_t kTileBits = BLK == 64 ? ~0ull : (1ull << BLK) - 1;
 
@@ -422,7 +426,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     f32x4 dqacc[C::QBW][C::DB];
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
-        const bool real = !kPadded || row0 + 16 * u + r < rows;
+        const bool real = !(kPadded || WIDE) || row0 + 16 * u + r < rows;
         const int i = real ? row0 + 16 * u + r : rows - 1;
 #pragma unroll
         for (int ks = 0; ks < C::KS; ++ks) {
@@ -454,11 +458,11 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         for (int db = 0; db < C::DB; ++db) dqacc[u][db] = zero4();
     }
 
-    int e0 = 0, e1 = qb + 1;  // WALK_DENSE: key blocks 0 .. qb
+    int e0 = 0, e1 = qlast + 1;  // WALK_DENSE: key blocks 0 .. qb
     if (a.walk == WALK_BAND) {
-        e0 = max(0, qb - band_blocks(a));
+        e0 = max(0, (WIDE ? 2 * qb : qb) - band_blocks(a));
     } else if (a.walk == WALK_LAYOUT) {
-        const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
+        const int64_t rp = (int64_t)lay * (a.nq + 1) + qlast;
         e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
         e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
     }
@@ -498,7 +502,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     auto walk = [&](auto pass) {
     constexpr bool kSumD = decltype(pass)::value == 0;  // the walk that sums D
     // two-stage ring; the next step's blocks are read one step ahead
-    RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * BLK),
+    RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * C::QROWS),
                              a.walk != WALK_LAYOUT};
     RowStep cur = steps.next();
     if (cur.a >= 0) load_step(cur, 0);
@@ -510,7 +514,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         const int j0 = kb * BLK;
         // a pair of summary halves is attended everywhere
         const bool masked =
-            cur.b < 0 && !block_full32(PAT, mp.part, a.dl, a.c, mp.w, qs0, qs0 + BLK - 1, j0, j0 + BLK - 1);
+            cur.b < 0 && !block_full32(PAT, mp.part, a.dl, a.c, mp.w, qs0, qs1, j0, j0 + BLK - 1);
         wait_loads_upto<0>();
         __syncthreads();  // this step is in LDS everywhere; the other stage is free
         if (nxt.a >= 0) load_step(nxt, st ^ 1);
@@ -710,7 +714,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         for (int u = 0; u < C::QBW; ++u) {
             const float nd = -sum_over_g(dsum[u]);
             nd4[u] = f32x4{nd, nd, nd, nd};
-            if (g == 0) ndelta[stat_index(a, b, h, row0 + 16 * u + r)] = nd;
+            if (g == 0 && (!WIDE || row0 + 16 * u + r < rows)) ndelta[stat_index(a, b, h, row0 + 16 * u + r)] = nd;
         }
         __syncthreads();  // every wave is done with the ring before it is refilled
     }
@@ -719,7 +723,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     // this lane holds dQ^T at d = 16 db + 4g + t for query row0 + 16u + r
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
-        if (kPadded && row0 + 16 * u + r >= rows) continue;
+        if ((kPadded || WIDE) && row0 + 16 * u + r >= rows) continue;
         uint16_t* drow = dq + base + (int64_t)(row0 + 16 * u + r) * a.ss;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db) {
@@ -1513,12 +1517,21 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
                                (const uint16_t*)o, (const uint16_t*)dout, lse, ndelta, nlse2, sched, ws.items,
                                ws.order);
         if (parts & BWD_DQ) (void)with_full_body<PAT>(a, [&](auto fb) {
-            auto dq_kernel = [&](auto sp) {
-                hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value>),
-                                   grid, dim3(DqCfg<D, BLK, PAT>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
+            auto dq_launch = [&](auto sp, auto wide) {
+                constexpr bool W = decltype(wide)::value;
+                const dim3 g = W ? dim3(grid.x, (grid.y + 1) / 2, grid.z) : grid;
+                hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value, W>),
+                                   g, dim3(DqCfg<D, BLK, PAT, W>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
                                    (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
                                    nlse2, ndelta, (uint16_t*)dq, (const uint16_t*)o, lse, sched, ws.items,
                                    ws.order);
+            };
+            auto dq_kernel = [&](auto sp) {
+                if constexpr (D == 64 && BLK == 64 && decltype(fb)::value && !decltype(sp)::value &&
+                              (PAT == FIXED || MODE == MODE_A1)) {
+                    if (wide_rows(a)) return dq_launch(sp, std::true_type{});
+                }
+                dq_launch(sp, std::false_type{});
             };
             if constexpr (PAT == FIXED) {
                 if (split) dq_kernel(std::true_type{});

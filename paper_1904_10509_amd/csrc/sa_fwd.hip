@@ -4,8 +4,8 @@
 // one running maximum and sum per row (online softmax) and saves
 // LSE = log(sum_j exp(s_ij)) for the recomputing backward (Sec. 5.4).
 //
-// bf16 path: one workgroup per (query block qb, head, batch), waves of 32
-// query rows (one wave of 16 rows for B = 16).  Per present key block kb:
+// bf16 path: one workgroup per (query block qb, head, batch), waves of 16 query
+// rows (or per two query blocks, waves of 32 rows: see wide_rows).  Per present key block kb:
 //   S^T = K_kb Q^T        (MFMA 16x16x32, K from LDS, Q fragment in VGPRs)
 //   mask (MASKED blocks), running max over the row, P = exp2(S - m)
 //   O^T += V_kb^T P^T     (MFMA; P^T is fed from the S^T results directly)
@@ -28,33 +28,31 @@ namespace {
 // Waves of 16 query rows: with four waves per 64-wide block the workgroup holds
 // more waves per SIMD (fewer registers each), and in the strided pattern a
 // block that holds one diagonal leaves each 16-row wave a single live chunk.
-template <int D, int BLK, int PAT>
+template <int D, int BLK, bool WIDE>
 struct FwdCfg {
-    // query rows per wave.  (32 rows per wave in the fixed pattern, each K / V
-    // operand read feeding two row blocks at two waves per SIMD, made the
-    // forward at n = 65,536 slower: 0.83 against 0.77 ms.)
-    static constexpr int RW = 16;
+    static constexpr int RW = WIDE ? 32 : 16;       // query rows per wave
+    static constexpr int QROWS = WIDE ? 2 * BLK : BLK;  // query rows per workgroup
     static constexpr int QBW = RW / 16;             // 16-row blocks per wave
-    static constexpr int NW = BLK / RW;             // waves per workgroup
+    static constexpr int NW = QROWS / RW;           // waves per workgroup
     static constexpr int NT = NW * 64;              // threads
     static constexpr int KS = D / 32;               // 32-deep steps over d for S
     static constexpr int KB = BLK / 16;             // 16-key blocks per tile
     static constexpr int KC = (BLK + 31) / 32;      // 32-key chunks for P V
     static constexpr int DB = D / 16;               // 16-wide d blocks of O
     static constexpr int NS = 2;                    // K / V ring stages
-    static constexpr int WAVES_PER_EU = RW == 32 ? 2 : 3;
+    static constexpr int WAVES_PER_EU = 3;
 };
 
 // grid: (heads, nq, batch).  Consecutive workgroups (dispatched round-robin
 // over the XCDs) share a query block index across heads, so with heads a
 // multiple of 8 each head stays on one XCD and its keys stay in that L2; a
 // dense walk takes a head's query blocks together instead (row_grid_item).
-template <int D, int BLK, int PAT, int MODE, bool FULL_BODY>
-__global__ void __launch_bounds__((FwdCfg<D, BLK, PAT>::NT)) __attribute__((amdgpu_waves_per_eu(FwdCfg<D, BLK, PAT>::WAVES_PER_EU)))
+template <int D, int BLK, int PAT, int MODE, bool FULL_BODY, bool WIDE>
+__global__ void __launch_bounds__((FwdCfg<D, BLK, WIDE>::NT)) __attribute__((amdgpu_waves_per_eu(FwdCfg<D, BLK, WIDE>::WAVES_PER_EU)))
 fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                 const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, uint16_t* __restrict__ o, float* __restrict__ lse) {
-    using C = FwdCfg<D, BLK, PAT>;
+    using C = FwdCfg<D, BLK, WIDE>;
     // K and V tiles in a two-stage ring: the next key block is in flight
     // while one is computed; one barrier per key block
     __shared__ __attribute__((aligned(16))) uint16_t sK[C::NS][BLK * D];
@@ -63,7 +61,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     constexpr uint64_t kTileBits = BLK == 64 ? ~0ull : (1ull << BLK) - 1;
     const uint32_t sK_base = lds_addr(&sK[0][0]), sV_base = lds_addr(&sV[0][0]);
 
-    const GridItem gi = row_grid_item(a);  // longest rows first
+    const GridItem gi = row_grid_item(a);  // longest rows first; WIDE: qb is a pair of query blocks
     const int h = __builtin_amdgcn_readfirstlane(gi.h), qb = __builtin_amdgcn_readfirstlane(gi.qb),
               b = __builtin_amdgcn_readfirstlane(gi.b);
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
@@ -74,9 +72,12 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     // residue classes run as strided A1: only that kernel may meet padding rows
     constexpr bool kPadded = PAT == STRIDED && MODE == MODE_A1;
     const int rows = kPadded ? head_rows(a, h) : a.n;
-    if (kPadded && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
-    const int row0 = qb * BLK + w * C::RW;  // first query row of this wave
-    const int qs0 = qb * BLK - a.qshift;    // first query row of the block as the masks see it
+    if (kPadded && !WIDE && qb * BLK >= rows) return;  // a class that ends before this block (uniform)
+    const int row0 = qb * C::QROWS + w * C::RW;  // first query row of this wave
+    // the query rows whose masks decide how a block is treated: the block's, or
+    // (wide) the wave's own
+    const int qs0 = (WIDE ? row0 : qb * BLK) - a.qshift, qs1 = qs0 + (WIDE ? C::RW : BLK) - 1;
+    const int qlast = WIDE ? min(2 * qb + 1, a.nq - 1) : qb;  // last query block (its row holds the others')
 
     bf16x8 qf[C::QBW][C::KS];
     f32x4 oacc[C::QBW][C::DB];
@@ -84,7 +85,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     RowLane rl[C::QBW];
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
-        const int i = kPadded ? min(row0 + 16 * u + r, rows - 1) : row0 + 16 * u + r;
+        const int i = kPadded || WIDE ? min(row0 + 16 * u + r, rows - 1) : row0 + 16 * u + r;
 #pragma unroll
         for (int ks = 0; ks < C::KS; ++ks) qf[u][ks] = ld_bf16x8(q + base + (int64_t)i * a.ss + ks * 32 + 8 * g);
 #pragma unroll
@@ -94,11 +95,11 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
         rl[u] = row_lane(row0 + 16 * u + r - a.qshift, a.dl);
     }
 
-    int e0 = 0, e1 = qb + 1;  // WALK_DENSE: key blocks 0 .. qb
+    int e0 = 0, e1 = qlast + 1;  // WALK_DENSE: key blocks 0 .. qb
     if (a.walk == WALK_BAND) {
-        e0 = max(0, qb - band_blocks(a));
+        e0 = max(0, (WIDE ? 2 * qb : qb) - band_blocks(a));
     } else if (a.walk == WALK_LAYOUT) {
-        const int64_t rp = (int64_t)lay * (a.nq + 1) + qb;
+        const int64_t rp = (int64_t)lay * (a.nq + 1) + qlast;
         e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
         e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
     }
@@ -135,7 +136,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     const float c2 = a.scale_log2;
     // two-stage ring; the next step's blocks are read one step ahead (scalar
     // loads, off the vector-memory counter the ring waits on)
-    RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * BLK),
+    RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * C::QROWS),
                              a.walk != WALK_LAYOUT};
     // strided blocks away from the band are single diagonals (see the step)
     const bool diag_far = PAT == STRIDED && mp.part != PART_A1 && a.l % BLK == 0;
@@ -151,7 +152,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
         const int j0 = kb * BLK;
         // a pair of summary halves is attended everywhere
         const bool masked =
-            cur.b < 0 && !block_full32(PAT, mp.part, a.dl, a.c, mp.w, qs0, qs0 + BLK - 1, j0, j0 + BLK - 1);
+            cur.b < 0 && !block_full32(PAT, mp.part, a.dl, a.c, mp.w, qs0, qs1, j0, j0 + BLK - 1);
         wait_loads_upto<0>();
         __syncthreads();  // this step is in LDS everywhere; the other stage is free
         if (nxt.a >= 0) load_step(nxt, st ^ 1);
@@ -353,8 +354,17 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
                 // multiplies: n = 1,048,576 forward 2.94 -> 2.90 ms.)
 #pragma unroll
                 for (int db = 0; db < C::DB; ++db) oacc[u][db] *= alpha;
+                if constexpr (WIDE) {
+#pragma unroll
+                    for (int kc = 0; kc < C::KC; ++kc)
+                        if (cls[u][kc] != CHUNK_NONE)
+#pragma unroll
+                            for (int db = 0; db < C::DB; ++db) oacc[u][db] = mfma_16x16x32(vt[kc][db], pf[u][kc], oacc[u][db]);
+                }
             }
 
+
+            if constexpr (!WIDE) {
             // O^T += V^T P^T
 #pragma unroll
             for (int kc = 0; kc < C::KC; ++kc) {
@@ -364,6 +374,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db) oacc[u][db] = mfma_16x16x32(vt[kc][db], pf[u][kc], oacc[u][db]);
                 }
+            }
             }
         };
         if (masked || !FULL_BODY) compute(std::false_type{});
@@ -376,7 +387,7 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
     for (int u = 0; u < C::QBW; ++u) {
         const int i = row0 + 16 * u + r;
         const float l_tot = sum_over_g(l_run[u]);
-        if (kPadded && i >= rows) continue;
+        if ((kPadded || WIDE) && i >= rows) continue;
         uint16_t* orow = o + base + (int64_t)i * a.ss;
         float* lrow = lse + stat_index(a, b, h, i);
         if (a.epilogue == EPI_MERGE) {
@@ -417,8 +428,17 @@ hipError_t launch_bf16(const AttnArgs& a, const void* q, const void* k, const vo
     return with_pattern_mode(a.pattern, a.mode, [&](auto pat, auto mode) {
         constexpr int PAT = decltype(pat)::value, MODE = decltype(mode)::value;
         return with_full_body<PAT>(a, [&](auto fb) {
-            hipLaunchKernelGGL((fwd_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value>), grid,
-                               dim3(FwdCfg<D, BLK, PAT>::NT), 0, stream, a, a.row_ptr, a.col_idx, (const uint16_t*)q,
+            if constexpr (D == 64 && BLK == 64 && decltype(fb)::value && (PAT == FIXED || MODE == MODE_A1)) {
+                if (wide_rows(a)) {
+                    hipLaunchKernelGGL((fwd_bf16_kernel<D, BLK, PAT, MODE, true, true>),
+                                       dim3((unsigned)a.heads, (unsigned)((a.nq + 1) / 2), (unsigned)a.batch),
+                                       dim3(FwdCfg<D, BLK, true>::NT), 0, stream, a, a.row_ptr, a.col_idx,
+                                       (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
+                    return hipGetLastError();
+                }
+            }
+            hipLaunchKernelGGL((fwd_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, false>), grid,
+                               dim3(FwdCfg<D, BLK, false>::NT), 0, stream, a, a.row_ptr, a.col_idx, (const uint16_t*)q,
                                (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
             return hipGetLastError();
         });

@@ -100,6 +100,30 @@ struct AttnArgs {
     const uint8_t* kind_t;
 };
 
+// Blocks before (row) or after (column) the diagonal one in the strided band.
+__host__ __device__ inline int band_blocks(const AttnArgs& a) { return (a.l - 1) / a.block + 1; }
+constexpr int kLongBand = 8;  // from here on a band's walks count as long
+
+// Whether a workgroup of the forward or the dQ kernel takes two query blocks (four
+// waves of 32 rows): where both walk the same blocks but for the diagonal's, i.e.
+// the strided band, and in the fixed pattern l-blocks of whole pairs.  A staged
+// tile then serves 128 rows, and in the forward each K / V operand read from LDS
+// feeds 32 rows instead of 16, at three waves per SIMD instead of four (with one
+// query block per workgroup the ring's LDS allowed 2.5, and 32 rows were slower).
+// Fixed n = 65,536, 8 heads: forward 0.712 -> 0.643 ms, dQ 0.736 -> 0.702; n =
+// 12,288, 16 heads: forward 110 -> 104 us; dense limit, n = 12,288, 16 heads:
+// forward 375 -> 343 us, backward 1,070 -> 1,020.  Half as many workgroups of twice
+// the length: kWideGroups of them keep the chip full to the end (1,024: 190 against
+// 189 us; 480, n = 4,096: 20.6 against 25.4), and a short band is over before the
+// wider reads pay (l = 128, 3 blocks: 25.5 against 29.2 us).
+constexpr int64_t kWideGroups = 1024;
+inline bool wide_rows(const AttnArgs& a) {
+    if (a.pattern == STRIDED ? a.walk != WALK_BAND || band_blocks(a) < kLongBand
+                             : a.walk != WALK_LAYOUT || a.l % 128 != 0)
+        return false;
+    return (int64_t)a.batch * a.heads * ((a.nq + 1) / 2) >= kWideGroups;
+}
+
 // The (head, query block, batch) of a row-view workgroup, on the grid
 // (heads, nq, batch).  The dispatcher hands consecutive workgroups to the 8
 // XCDs in turn, so workgroup L (x fastest) runs on XCD L mod 8.  A walk of
@@ -108,18 +132,26 @@ struct AttnArgs {
 // places s = L / 8 on one XCD: its keys then stay in that XCD's L2 while all
 // its query blocks walk them, instead of leaving it between the query-block
 // generations of the plain order.  Needs batch x heads a multiple of 8;
-// otherwise, and for other walks, the plain order.  Longest rows first.
+// otherwise, and for other walks, query blocks (pairs of them, for a grid of half
+// as many) from the longest rows down, every (batch, head) of one before the next:
+// with the batch outermost its last element's long rows started late (dense
+// limit, n = 12,288, 2 x 8 heads: forward 400 -> 375 us, backward 1,145 -> 1,070).
+// A band of few blocks keeps the batch outermost: its rows are equal, and
+// neighbouring ones share their keys in L2 (n = 12,288, l = 128: backward 2 to 4%).
 struct GridItem {
     int h, qb, b;
 };
 __device__ inline GridItem row_grid_item(const AttnArgs& a) {
+    const uint64_t L = blockIdx.x + (uint64_t)gridDim.x * (blockIdx.y + (uint64_t)gridDim.y * blockIdx.z);
     if (a.walk == WALK_DENSE && ((int64_t)a.batch * a.heads) % 8 == 0) {
-        const uint64_t L = blockIdx.x + (uint64_t)gridDim.x * (blockIdx.y + (uint64_t)gridDim.y * blockIdx.z);
         const uint64_t s = L / 8;
         const uint64_t u = (s / (uint64_t)a.nq) * 8 + L % 8;  // (batch, head) unit
         return {(int)(u % (uint64_t)a.heads), a.nq - 1 - (int)(s % (uint64_t)a.nq), (int)(u / (uint64_t)a.heads)};
     }
-    return {(int)blockIdx.x, a.nq - 1 - (int)blockIdx.y, (int)blockIdx.z};
+    if (a.walk == WALK_BAND && band_blocks(a) < kLongBand)
+        return {(int)blockIdx.x, (int)(gridDim.y - 1 - blockIdx.y), (int)blockIdx.z};
+    const uint64_t units = (uint64_t)a.batch * a.heads, y = L / units, u = L - y * units;
+    return {(int)(u % (uint64_t)a.heads), (int)(gridDim.y - 1 - y), (int)(u / (uint64_t)a.heads)};
 }
 
 // First element of (batch b, head h) in the tensors.
@@ -139,8 +171,6 @@ __host__ __device__ inline int head_rows(const AttnArgs& a, int h) {
     return a.seq > 0 ? (a.seq - 1 - h) / a.heads + 1 : a.n;
 }
 
-// Blocks before (row) or after (column) the diagonal one in the strided band.
-__host__ __device__ inline int band_blocks(const AttnArgs& a) { return (a.l - 1) / a.block + 1; }
 
 // Layout that head h reads.
 __host__ __device__ inline int head_layout(const AttnArgs& a, int h) { return layout_of_head(a.mode, a.sub, h); }

@@ -350,12 +350,13 @@ bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, 
 // and each K / V operand read from LDS then serves 32 rows (16 rows at three
 // waves per SIMD made the fixed backward at n = 65,536 slower: 2.30 against
 // 2.24 ms).
-template <int D, int BLK, int PAT, bool WIDE = false>
+template <int D, int BLK, int PAT, bool WIDE = false, int PH = 1>
 struct DqCfg {
     static constexpr int RW = !WIDE && (BLK < 32 || PAT == STRIDED) ? 16 : 32;  // query rows per wave
     static constexpr int QROWS = WIDE ? 2 * BLK : BLK;  // query rows per workgroup
     static constexpr int QBW = RW / 16;
-    static constexpr int NW = QROWS / RW;
+    static constexpr int RN = QROWS / RW;  // waves along the rows
+    static constexpr int NW = RN * PH;     // PH of them along the walk
     static constexpr int NT = NW * 64;
     static constexpr int KS = D / 32;
     static constexpr int KB = BLK / 16;
@@ -374,12 +375,15 @@ struct DqCfg {
 //
 // a.row_stats: the kernel does the pre kernel's work for its own rows, D_i =
 // dO_i . O_i and the LSE in base 2 (it holds dO_i already), and writes both for
-// the dK / dV kernel; its first layout_count workgroups build the dK / dV
-// schedule.  The launcher sets it when the grid covers every row and at least
+// the dK / dV kernel; layout_count of its workgroups build the dK / dV schedule.  The launcher sets it when the grid covers every row and at least
 // that many workgroups, and then launches no pre kernel.
-template <int D, int BLK, int PAT, int MODE, bool FULL_BODY, bool SPLIT, bool WIDE>
-__global__ void __launch_bounds__((DqCfg<D, BLK, PAT, WIDE>::NT))
-    __attribute__((amdgpu_waves_per_eu(DqCfg<D, BLK, PAT, WIDE>::WAVES_PER_EU)))
+//
+// PH > 1 (see walk_phases): PH waves share a row's walk, wave (phase) p taking its
+// entries p, p + PH, ..., each with a ring of its own; their sums of D and of dQ
+// are combined in the order of the phases.
+template <int D, int BLK, int PAT, int MODE, bool FULL_BODY, bool SPLIT, bool WIDE, int PH>
+__global__ void __launch_bounds__((DqCfg<D, BLK, PAT, WIDE, PH>::NT))
+    __attribute__((amdgpu_waves_per_eu(DqCfg<D, BLK, PAT, WIDE, PH>::WAVES_PER_EU)))
 bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                    const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -387,13 +391,19 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                    uint16_t* __restrict__ dq, const uint16_t* __restrict__ o, const float* __restrict__ lse,
                    unsigned long long* __restrict__ queue, int32_t* __restrict__ items,
                    int32_t* __restrict__ order) {
-    using C = DqCfg<D, BLK, PAT, WIDE>;
+    using C = DqCfg<D, BLK, PAT, WIDE, PH>;
     if (a.row_stats && queue) {  // uniform over the workgroup
+        // by the workgroups of the shortest rows where the whole grid runs at
+        // once, else by some in its middle: before one of the longest rows (the
+        // first workgroups) it lengthens the launch, after all others too
         const int64_t wg = blockIdx.x + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
-        if (wg < layout_count(a.mode, a.sub)) build_schedule(a, (int)wg, queue, items, order);
+        const int64_t all = (int64_t)gridDim.x * gridDim.y * gridDim.z;
+        const int layouts = layout_count(a.mode, a.sub);
+        const int64_t first = all <= 768 ? all - layouts : (all - layouts) / 2;
+        if (wg >= first && wg < first + layouts) build_schedule(a, (int)(wg - first), queue, items, order);
     }
-    __shared__ __attribute__((aligned(16))) uint16_t sK[C::NS][BLK * D];
-    __shared__ __attribute__((aligned(16))) uint16_t sV[C::NS][BLK * D];
+    __shared__ __attribute__((aligned(16))) uint16_t sK[C::NS * PH][BLK * D];
+    __shared__ __attribute__((aligned(16))) uint16_t sV[C::NS * PH][BLK * D];
     constexpr uint32_t kTileBytes = BLK * D * 2;
     const uint32_t sK_base = lds_addr(&sK[0][0]), sV_base = lds_addr(&sV[0][0]);
 
@@ -401,7 +411,9 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     const int h = __builtin_amdgcn_readfirstlane(gi.h), qb = __builtin_amdgcn_readfirstlane(gi.qb),
               b = __builtin_amdgcn_readfirstlane(gi.b);
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
-    const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int w = wave % C::RN, phase = wave / C::RN;
+    static_assert(PH == 1 || BLK < 64, "pairs of summary halves are not split into phases");
     const int lay = head_layout(a, h);
     const MaskParams mp = head_mask_params(a, PAT, MODE, h);
     const int64_t base = head_base(a, b, h);
@@ -444,7 +456,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                 part += dot_bf16x8(of[u][ks], ld_bf16x8(o + base + (int64_t)i * a.ss + ks * 32 + 8 * g));
             nd = -sum_over_g(part);
             nl2[u] = -lse[si] * kLog2e;  // an empty row (LSE = -inf) gives +inf; its items are all masked
-            if (g == 0 && real) {
+            if (g == 0 && real && phase == 0) {
                 ndelta[si] = nd;
                 nlse2[si] = nl2[u];
             }
@@ -466,12 +478,12 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         e0 = __builtin_amdgcn_readfirstlane(row_ptr[rp]);
         e1 = __builtin_amdgcn_readfirstlane(row_ptr[rp + 1]);
     }
-    TileLoader<D, BLK, C::NW> ld;
+    TileLoader<D, BLK, C::RN> ld;
     ld.init(a.ss, w, lane);
     // A step stages one block, or two summary halves (see RowStepper) as one tile
     constexpr bool kPairs = PAT == FIXED && BLK == 64;
     auto load_step = [&](RowStep s, int stage) {
-        const uint32_t kdst = sK_base + stage * kTileBytes, vdst = sV_base + stage * kTileBytes;
+        const uint32_t slot = (stage * PH + phase) * kTileBytes, kdst = sK_base + slot, vdst = sV_base + slot;
         if (!kPairs || s.b < 0) {
             const int64_t kbase = base + (int64_t)s.a * BLK * a.ss;
             if (kPadded && rows - s.a * BLK < BLK) {
@@ -502,13 +514,14 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
     auto walk = [&](auto pass) {
     constexpr bool kSumD = decltype(pass)::value == 0;  // the walk that sums D
     // two-stage ring; the next step's blocks are read one step ahead
-    RowStepper<kPairs> steps{col_idx, e0, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * C::QROWS),
-                             a.walk != WALK_LAYOUT};
+    RowStepper<kPairs> steps{col_idx, e0 + phase, e1, RowStepper<kPairs>::pair_bound(mp, a.dl, qb * C::QROWS),
+                             a.walk != WALK_LAYOUT, PH};
+    int left = PH > 1 ? (e1 - e0 + PH - 1) / PH : 0;  // steps of the longest phase, all of which meet its barriers
     RowStep cur = steps.next();
     if (cur.a >= 0) load_step(cur, 0);
     two_stage_while([&](auto stage) {
         constexpr int st = decltype(stage)::value;
-        if (cur.a < 0) return false;
+        if (PH > 1 ? left-- == 0 : cur.a < 0) return false;
         const RowStep nxt = steps.next();
         const int kb = cur.a;
         const int j0 = kb * BLK;
@@ -518,8 +531,9 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         wait_loads_upto<0>();
         __syncthreads();  // this step is in LDS everywhere; the other stage is free
         if (nxt.a >= 0) load_step(nxt, st ^ 1);
-        const uint16_t* tK = sK[st];
-        const uint16_t* tV = sV[st];
+        if (PH > 1 && cur.a < 0) return true;  // this phase has run out
+        const uint16_t* tK = sK[st * PH + (PH > 1 ? phase : 0)];
+        const uint16_t* tV = sV[st * PH + (PH > 1 ? phase : 0)];
         if constexpr (PAT == STRIDED) {
             // a single diagonal (see the forward): per row one score, one dS and
             // dQ += dS k as a rank-1 step in registers
@@ -712,13 +726,42 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
         // the lanes of a row hold disjoint keys: D_i is the sum over them
 #pragma unroll
         for (int u = 0; u < C::QBW; ++u) {
-            const float nd = -sum_over_g(dsum[u]);
+            float nd = -sum_over_g(dsum[u]);
+            if constexpr (PH > 1) {
+                __shared__ float sSum[PH][C::RN][C::QBW][16];
+                if (g == 0) sSum[phase][w][u][r] = nd;
+                __syncthreads();
+                nd = 0.f;
+#pragma unroll
+                for (int x = 0; x < PH; ++x) nd += sSum[x][w][u][r];
+            }
             nd4[u] = f32x4{nd, nd, nd, nd};
-            if (g == 0 && (!WIDE || row0 + 16 * u + r < rows)) ndelta[stat_index(a, b, h, row0 + 16 * u + r)] = nd;
+            if (g == 0 && phase == 0 && (!WIDE || row0 + 16 * u + r < rows)) ndelta[stat_index(a, b, h, row0 + 16 * u + r)] = nd;
         }
         __syncthreads();  // every wave is done with the ring before it is refilled
     }
     walk(std::integral_constant<int, 1>{});
+    if constexpr (PH > 1) {
+        static_assert(sizeof(sK) >= (size_t)(PH - 1) * C::RN * C::QBW * C::DB * 64 * sizeof(f32x4), "sums fit the ring");
+        __syncthreads();
+        f32x4* red = reinterpret_cast<f32x4*>(&sK[0][0]);
+        if (phase > 0) {
+#pragma unroll
+            for (int u = 0; u < C::QBW; ++u)
+#pragma unroll
+                for (int db = 0; db < C::DB; ++db)
+                    red[((((phase - 1) * C::RN + w) * C::QBW + u) * C::DB + db) * 64 + lane] = dqacc[u][db];
+        }
+        __syncthreads();
+        if (phase > 0) return;
+#pragma unroll
+        for (int x = 0; x < PH - 1; ++x)
+#pragma unroll
+            for (int u = 0; u < C::QBW; ++u)
+#pragma unroll
+                for (int db = 0; db < C::DB; ++db)
+                    dqacc[u][db] += red[(((x * C::RN + w) * C::QBW + u) * C::DB + db) * 64 + lane];
+    }
 
     // this lane holds dQ^T at d = 16 db + 4g + t for query row0 + 16u + r
 #pragma unroll
@@ -743,7 +786,7 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
 // group (all of its keys are summary keys or none is), so whole waves skip
 // their products; in the strided pattern a block holding one diagonal leaves
 // each 16-key wave a single live 32-query chunk.
-template <int D, int BLK, int PAT>
+template <int D, int BLK, int PAT, int PH = 1>
 struct DkvCfg {
     // keys per wave.  (32 keys per wave, two key groups sharing every Q / dO
     // operand read, needs about 290 registers: at one wave per SIMD it made the
@@ -752,7 +795,8 @@ struct DkvCfg {
     // against 2.18 ms; the half and pair logic below handles both widths.)
     static constexpr int KW = 16;
     static constexpr int KBW = KW / 16;         // 16-key blocks per wave
-    static constexpr int NW = BLK / KW;         // waves
+    static constexpr int KN = BLK / KW;         // waves along the keys
+    static constexpr int NW = KN * PH;          // PH of them along the column
     static constexpr int NT = NW * 64;
     static constexpr int KS = D / 32;           // 32-deep steps over d
     static constexpr int QB = BLK / 16;         // 16-query blocks per tile
@@ -766,9 +810,13 @@ struct DkvCfg {
 // SPLIT: P and dS enter the dV and dK products as a high and a low bf16 part
 // (two products each), for calls whose long key columns are attended by rows
 // with few keys (see split_products).
-template <int D, int BLK, int PAT, int MODE, bool SPLIT>
-__global__ void __launch_bounds__((DkvCfg<D, BLK, PAT>::NT))
-    __attribute__((amdgpu_waves_per_eu(DkvCfg<D, BLK, PAT>::WAVES_PER_EU)))
+//
+// PH > 1 (see walk_phases): PH waves share a key group's column, wave (phase) p
+// taking its query blocks p, p + PH, ..., each with a ring of its own; their sums
+// are combined in the order of the phases.
+template <int D, int BLK, int PAT, int MODE, bool SPLIT, int PH>
+__global__ void __launch_bounds__((DkvCfg<D, BLK, PAT, PH>::NT))
+    __attribute__((amdgpu_waves_per_eu(DkvCfg<D, BLK, PAT, PH>::WAVES_PER_EU)))
 bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ row_idx,
                      const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -776,15 +824,15 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                      uint16_t* __restrict__ dk, uint16_t* __restrict__ dv,
                      unsigned long long* __restrict__ queue, const int32_t* __restrict__ items,
                      const int32_t* __restrict__ order) {
-    using C = DkvCfg<D, BLK, PAT>;
+    using C = DkvCfg<D, BLK, PAT, PH>;
     constexpr bool kHalves = PAT == FIXED && BLK == 64;  // items may be 32-key halves
     static_assert(!kHalves || (C::QC == 2 && ((C::NW == 4 && C::KBW == 1) || (C::NW == 2 && C::KBW == 2))),
                   "half items: 4 waves of 16 keys or 2 of 32");
     constexpr int kHalfWaves = C::NW >= 2 ? C::NW / 2 : 1;  // waves per 32-key half in a pair
-    __shared__ __attribute__((aligned(16))) uint16_t sQ[C::NS][BLK * D];
-    __shared__ __attribute__((aligned(16))) uint16_t sdO[C::NS][BLK * D];
-    __shared__ __attribute__((aligned(16))) float sL[C::NS][64];
-    __shared__ __attribute__((aligned(16))) float sDl[C::NS][64];
+    __shared__ __attribute__((aligned(16))) uint16_t sQ[C::NS * PH][BLK * D];
+    __shared__ __attribute__((aligned(16))) uint16_t sdO[C::NS * PH][BLK * D];
+    __shared__ __attribute__((aligned(16))) float sL[C::NS * PH][64];
+    __shared__ __attribute__((aligned(16))) float sDl[C::NS * PH][64];
     __shared__ unsigned long long sItem[2];
     constexpr uint32_t kTileBytes = BLK * D * 2;
     constexpr uint64_t kTileBits = BLK == 64 ? ~0ull : (1ull << BLK) - 1;
@@ -792,10 +840,12 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
     const uint32_t sL_base = lds_addr(&sL[0][0]), sDl_base = lds_addr(&sDl[0][0]);
 
     const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
-    const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int w = wave % C::KN, phase = PH > 1 ? wave / C::KN : 0;
+    static_assert(PH == 1 || !kHalves, "half items are not split into phases");
     const int64_t bh_count = (int64_t)a.batch * a.heads;
     const float c2 = a.scale_log2;
-    TileLoader<D, BLK, C::NW> ld;
+    TileLoader<D, BLK, C::KN> ld;
     ld.init(a.ss, w, lane);
     TileReader<D> rd;
     rd.init(g, r);
@@ -974,7 +1024,7 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
         // every block; in a pair, the same groups of its block's half, for
         // every query.
         auto kgrp = [&](int kbw) {
-            return half == 0 ? C::NW * kbw + w : 2 * (half - 1) + (C::KBW == 2 ? kbw : (w & 1));
+            return half == 0 ? C::KN * kbw + w : 2 * (half - 1) + (C::KBW == 2 ? kbw : (w & 1));
         };
         auto key_of = [&](int kbw) { return kb_w * BLK + 16 * kgrp(kbw) + r; };
 
@@ -1044,27 +1094,28 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
             const int64_t qbase = base + (int64_t)qb * BLK * a.ss;
             const int n_valid = kPadded ? min(BLK, rows - qb * BLK) : BLK;
             if (kPadded && n_valid < BLK) {
-                ld.issue_rows(q + qbase, sQ_base + stage * kTileBytes, a.ss, n_valid, lane);
-                ld.issue_rows(dout + qbase, sdO_base + stage * kTileBytes, a.ss, n_valid, lane);
+                ld.issue_rows(q + qbase, sQ_base + (stage * PH + phase) * kTileBytes, a.ss, n_valid, lane);
+                ld.issue_rows(dout + qbase, sdO_base + (stage * PH + phase) * kTileBytes, a.ss, n_valid, lane);
             } else {
-                ld.issue(q + qbase, sQ_base + stage * kTileBytes);
-                ld.issue(dout + qbase, sdO_base + stage * kTileBytes);
+                ld.issue(q + qbase, sQ_base + (stage * PH + phase) * kTileBytes);
+                ld.issue(dout + qbase, sdO_base + (stage * PH + phase) * kTileBytes);
             }
             const int64_t st0 = stat_index(a, b, h, (int64_t)qb * BLK);
-            if (w == 0) load_row_stats_async(nlse2 + st0, n_valid, sL_base + stage * 256u, lane, (uint32_t)a.lse_ss);
-            if (w == C::NW - 1)
-                load_row_stats_async(ndelta + st0, n_valid, sDl_base + stage * 256u, lane, (uint32_t)a.lse_ss);
+            if (w == 0) load_row_stats_async(nlse2 + st0, n_valid, sL_base + (stage * PH + phase) * 256u, lane, (uint32_t)a.lse_ss);
+            if (w == C::KN - 1)
+                load_row_stats_async(ndelta + st0, n_valid, sDl_base + (stage * PH + phase) * 256u, lane, (uint32_t)a.lse_ss);
         };
 
         wait_loads_upto<0>();  // register loads done before the ring starts
         // two-stage ring: the next block's index is read one step ahead (a
         // scalar load, off the vector-memory counter the ring waits on)
-        int qb_next = len > 0 ? query_block(0) : 0;
-        if (len > 0) load_block(qb_next, 0);
-        two_stage_loop(len, [&](auto stage, int sidx) {
+        int qb_next = phase < len ? query_block(phase) : 0;
+        if (phase < len) load_block(qb_next, 0);
+        two_stage_loop((len + PH - 1) / PH, [&](auto stage, int step) {
             constexpr int st = decltype(stage)::value;
+            const int sidx = step * PH + phase;  // this phase's step of the column
             const int qb = qb_next;
-            qb_next = sidx + 1 < len ? query_block(sidx + 1) : 0;
+            qb_next = sidx + PH < len ? query_block(sidx + PH) : 0;
             const int i0 = qb * BLK - a.qshift;  // first query row of the block as the masks see it
             // a pair's keys are summary keys, attended by every query of a block
             // away from both key blocks' l-blocks
@@ -1077,11 +1128,12 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                      : !block_full32(PAT, mp.part, a.dl, a.c, mp.w, i0, i0 + BLK - 1, kb * BLK, kb * BLK + BLK - 1);
             wait_loads_upto<0>();
             __syncthreads();  // block sidx is in LDS everywhere; the other stage is free
-            if (sidx + 1 < len) load_block(qb_next, st ^ 1);
-            const uint16_t* tQ = sQ[st];
-            const uint16_t* tO = sdO[st];
-            const float* tL = sL[st];
-            const float* tD = sDl[st];
+            if (sidx + PH < len) load_block(qb_next, st ^ 1);
+            if (PH > 1 && sidx >= len) return;  // this phase has run out
+            const uint16_t* tQ = sQ[st * PH + phase];
+            const uint16_t* tO = sdO[st * PH + phase];
+            const float* tL = sL[st * PH + phase];
+            const float* tD = sDl[st * PH + phase];
             if constexpr (PAT == STRIDED) {
                 // a single diagonal (see the forward): key kk of the block meets
                 // query kk only, so dV += p dO and dK += dS q are rank-1 steps in
@@ -1349,9 +1401,35 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                 }
             }
         }
+        if constexpr (PH > 1) {
+            static_assert(C::KBW == 1 && sizeof(sQ) >= (size_t)(PH - 1) * C::KN * C::DB * 64 * sizeof(f32x4) &&
+                              sizeof(sdO) == sizeof(sQ),
+                          "sums fit the rings");
+            __syncthreads();
+            f32x4* redv = reinterpret_cast<f32x4*>(&sQ[0][0]);
+            f32x4* redk = reinterpret_cast<f32x4*>(&sdO[0][0]);
+            if (phase > 0) {
+#pragma unroll
+                for (int db = 0; db < C::DB; ++db) {
+                    redv[(((phase - 1) * C::KN + w) * C::DB + db) * 64 + lane] = dvacc[0][db];
+                    redk[(((phase - 1) * C::KN + w) * C::DB + db) * 64 + lane] = dkacc[0][db];
+                }
+            }
+            __syncthreads();
+            if (phase == 0) {
+#pragma unroll
+                for (int x = 0; x < PH - 1; ++x)
+#pragma unroll
+                    for (int db = 0; db < C::DB; ++db) {
+                        dvacc[0][db] += redv[((x * C::KN + w) * C::DB + db) * 64 + lane];
+                        dkacc[0][db] += redk[((x * C::KN + w) * C::DB + db) * 64 + lane];
+                    }
+            }
+        }
         // this lane holds dV^T / dK^T at d = 16 db + 4g + t for key key_of(kbw)
 #pragma unroll
         for (int kbw = 0; kbw < C::KBW; ++kbw) {
+            if (PH > 1 && phase > 0) break;  // summed into phase 0
             if (single && qhalf == 1) break;  // written by the wave of the other query half
             const int j = key_of(kbw);
             if (kPadded && j >= rows) continue;
@@ -1451,6 +1529,23 @@ inline bool split_products(const AttnArgs& a) {
     return w > 0.15;
 }
 
+// Whether four waves share each row's (dQ) and each key group's (dK / dV) walk, in
+// the fixed pattern with B < 64.  There only the c / l summary columns of a head are
+// long, and a workgroup of one or two waves walks each alone.  The rings of four
+// phases take a compute unit's LDS at d = 128, B = 32 (one workgroup), half of it or
+// less at smaller sizes, so this pays only while the long columns are few: up to
+// kPhaseColumns, a third of it at d = 128, B = 32.  Backward before and after: 8 heads
+// of 128, n = 3,072, l = 128, c = 32, B = 32 114 -> 94 us (192 columns), 12 heads 117 ->
+// 127 (288); d = 64, n = 20,000, 4 heads 1,017 -> 849 (568), n = 8,384, 32 heads 346 ->
+// 586 (2,080); d = 128, B = 16, n = 4,096, l = 64, c = 8, 4 heads 402 -> 160.
+constexpr int64_t kPhaseColumns = 600;
+inline bool walk_phases(const AttnArgs& a) {
+    if (a.pattern != FIXED || a.mode == MODE_A1) return false;
+    const int64_t heads = a.mode == MODE_INTERLEAVED ? a.heads / 2 : a.heads;
+    const int64_t columns = a.batch * heads * ((int64_t)a.n / a.l) * ((a.c + a.block - 1) / a.block);
+    return columns <= (a.d * a.block > 2048 ? kPhaseColumns / 3 : kPhaseColumns);
+}
+
 template <int D, int BLK>
 hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, const void* v,
                            const void* o, const void* dout, const float* lse, void* dq, void* dk,
@@ -1468,9 +1563,15 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
     const bool split = split_products(a);
     return with_pattern_mode(a.pattern, a.mode, [&](auto pat, auto mode) {
         constexpr int PAT = decltype(pat)::value, MODE = decltype(mode)::value;
+        constexpr int PHASES = PAT == FIXED && BLK < 64 && MODE != MODE_A1 ? 4 : 1;
+        const bool phases = PHASES > 1 && walk_phases(a);
         const int64_t slots =
-            split ? resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, PAT == FIXED>>(DkvCfg<D, BLK, PAT>::NT)
-                  : resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, false>>(DkvCfg<D, BLK, PAT>::NT);
+            phases ? (split ? resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, PAT == FIXED, PHASES>>(
+                                  DkvCfg<D, BLK, PAT, PHASES>::NT)
+                            : resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, false, PHASES>>(
+                                  DkvCfg<D, BLK, PAT, PHASES>::NT))
+            : split ? resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, PAT == FIXED, 1>>(DkvCfg<D, BLK, PAT>::NT)
+                    : resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, false, 1>>(DkvCfg<D, BLK, PAT>::NT);
         // A band walk of long columns, and a dense walk (the residue classes)
         // of at least 8 blocks, take one workgroup per column instead of the
         // persistent grid: the hardware then overlaps one column's register
@@ -1517,11 +1618,13 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
                                (const uint16_t*)o, (const uint16_t*)dout, lse, ndelta, nlse2, sched, ws.items,
                                ws.order);
         if (parts & BWD_DQ) (void)with_full_body<PAT>(a, [&](auto fb) {
-            auto dq_launch = [&](auto sp, auto wide) {
+            auto dq_launch = [&](auto sp, auto wide, auto ph) {
                 constexpr bool W = decltype(wide)::value;
+                constexpr int PH = decltype(ph)::value;
                 const dim3 g = W ? dim3(grid.x, (grid.y + 1) / 2, grid.z) : grid;
-                hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value, W>),
-                                   g, dim3(DqCfg<D, BLK, PAT, W>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
+                hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value, W,
+                                                       PH>),
+                                   g, dim3(DqCfg<D, BLK, PAT, W, PH>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
                                    (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
                                    nlse2, ndelta, (uint16_t*)dq, (const uint16_t*)o, lse, sched, ws.items,
                                    ws.order);
@@ -1529,9 +1632,12 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
             auto dq_kernel = [&](auto sp) {
                 if constexpr (D == 64 && BLK == 64 && decltype(fb)::value && !decltype(sp)::value &&
                               (PAT == FIXED || MODE == MODE_A1)) {
-                    if (wide_rows(a)) return dq_launch(sp, std::true_type{});
+                    if (wide_rows(a)) return dq_launch(sp, std::true_type{}, std::integral_constant<int, 1>{});
                 }
-                dq_launch(sp, std::false_type{});
+                if constexpr (PHASES > 1) {
+                    if (phases) return dq_launch(sp, std::false_type{}, std::integral_constant<int, PHASES>{});
+                }
+                dq_launch(sp, std::false_type{}, std::integral_constant<int, 1>{});
             };
             if constexpr (PAT == FIXED) {
                 if (split) dq_kernel(std::true_type{});
@@ -1541,11 +1647,18 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
             }
             return hipSuccess;
         });
-        auto dkdv = [&](auto sp) {
-            hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, decltype(sp)::value>), dim3(qgrid),
-                               dim3(DkvCfg<D, BLK, PAT>::NT), 0, stream, ak, a.col_ptr, a.row_idx, (const uint16_t*)q,
+        auto dkdv_launch = [&](auto sp, auto ph) {
+            constexpr int PH = decltype(ph)::value;
+            hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, decltype(sp)::value, PH>), dim3(qgrid),
+                               dim3(DkvCfg<D, BLK, PAT, PH>::NT), 0, stream, ak, a.col_ptr, a.row_idx, (const uint16_t*)q,
                                (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, nlse2, ndelta,
                                (uint16_t*)dk, (uint16_t*)dv, ws.queue, ws.items, ws.order);
+        };
+        auto dkdv = [&](auto sp) {
+            if constexpr (PHASES > 1) {
+                if (phases) return dkdv_launch(sp, std::integral_constant<int, PHASES>{});
+            }
+            dkdv_launch(sp, std::integral_constant<int, 1>{});
         };
         if (!(parts & BWD_DKDV)) {
         } else if constexpr (PAT == FIXED) {

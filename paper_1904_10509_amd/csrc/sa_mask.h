@@ -153,6 +153,7 @@ struct RowStepper {
     int e, e1;    // next entry, end of the row
     int far_end;  // pairs are formed below this key block; 0: no pairs
     bool dense;   // no layout: entry e is key block e
+    int stride = 1;  // entries from one step to the next (without pairs)
     __device__ static int pair_bound(const MaskParams& p, const DivL& dl, int i0) {
         if (p.pattern != FIXED || p.part == PART_A1 || p.c != 32 || p.l % 64 != 0 || p.w % 32 != 0) return 0;
         return (i0 - mod_l(dl, i0)) / 64;
@@ -161,7 +162,7 @@ struct RowStepper {
         RowStep s{-1, -1};
         if (e >= e1) return s;
         s.a = dense ? e : __builtin_amdgcn_readfirstlane(col_idx[e]);
-        ++e;
+        e += PAIRS ? 1 : stride;
         if constexpr (PAIRS) {
             if (e < e1) {
                 const int kb = __builtin_amdgcn_readfirstlane(col_idx[e]);  // entries ascend: kb > s.a

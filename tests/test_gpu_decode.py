@@ -62,6 +62,29 @@ def test_decode_matches_oracle_rows(pattern, mode, n, l, c, d, dtype, batch, hea
         check_lse(f"{label} lse", got_lse, lse_ref, dtype)
 
 
+# Launch rules of a step: |S_pos| = 256 is one range (o and LSE written by the
+# split kernel), 257 two; up to 256 workgroups have sixteen waves each, more
+# have four; 2,100 keys in nine ranges do not divide among the combine's groups.
+@pytest.mark.parametrize("d,dtype,batch,heads,keys", [
+    (32, torch.float32, 2, 128, 256), (32, torch.float32, 1, 257, 256), (32, torch.bfloat16, 1, 128, 257),
+    (64, torch.bfloat16, 3, 43, 257), (64, torch.bfloat16, 1, 1, 2100), (128, torch.bfloat16, 2, 2, 2100),
+    (128, torch.float32, 1, 2, 1), (64, torch.float32, 1, 2, 31),
+])
+def test_decode_launch_rules(d, dtype, batch, heads, keys):
+    dev = device()
+    n = keys
+    x = make_inputs(batch, heads, n, d, dtype, seed=n + d + heads)
+    q = x["q"][:, :, n - 1, :].contiguous().to(dev)
+    o, lse = sa.decode(q, x["k"].to(dev), x["v"].to(dev), n - 1, max(n, 2), 0, S, A1, d ** -0.5)
+    torch.cuda.synchronize()
+    rows = np.array([(b, h, n - 1) for b in range(batch) for h in range(heads)])
+    o_ref, lse_ref = orc_mod.forward_rows(*oracle_inputs(x)[:3], rows, pattern=S, mode=A1, l=max(n, 2), c=0,
+                                          scale=d ** -0.5)
+    label = f"decode keys {keys} b{batch} h{heads} d{d} {str(dtype)[6:]}"
+    check(f"{label} o", to64(o).reshape(-1, d), o_ref, dtype)
+    check_lse(f"{label} lse", to64(lse).reshape(-1), lse_ref, dtype)
+
+
 def test_decode_empty_set_and_views():
     """Fixed A2 before the first summary column: empty S_pos gives o = 0 and
     LSE = -inf.  A cache that is a view into a longer buffer (larger sequence

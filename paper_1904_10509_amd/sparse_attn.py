@@ -109,6 +109,8 @@ def _ptr(t):
 
 
 def _stream(stream, device):
+    if stream is None and device.type == "cuda":  # the handle alone, without a torch.cuda.Stream around it
+        return torch._C._cuda_getCurrentRawStream(device.index)
     if stream is None:
         stream = torch.cuda.current_stream(device)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
@@ -119,9 +121,17 @@ def _strides(*tensors):
     first in shape, element type, device and strides (d contiguous); raises
     ValueError otherwise, before anything reaches the library."""
     ref = tensors[0]
-    if ref.dim() != 4:
+    shape, st, dtype, device = ref.shape, ref.stride(), ref.dtype, ref.device
+    if len(shape) != 4:
         raise ValueError("tensors must be [batch, heads, n, d]")
-    st = ref.stride()
+    # each attribute of a tensor is a call into torch: the first tensor's are read
+    # once and the others' once each, and what differs is looked for only then
+    if device.type == "cuda" and st[3] == 1:
+        for t in tensors[1:]:
+            if t.shape != shape or t.stride() != st or t.dtype != dtype or t.device != device:
+                break
+        else:
+            return (ctypes.c_int64 * 3)(st[0], st[1], st[2])
     for t in tensors:
         if t.dim() != 4 or t.shape != ref.shape:
             raise ValueError(f"tensor of shape {tuple(t.shape)} where {tuple(ref.shape)} is expected")
@@ -369,14 +379,19 @@ def decode(q, k_cache, v_cache, pos, stride_l, summary_c, pattern, head_mode, so
         raise ValueError("out must match q in shape and strides")
     lse = torch.empty((b, h), dtype=torch.float32, device=q.device) if lse is None else lse
     dtype = _dtype_code(q)
-    need = sparse_attn_decode_workspace_size(pos, stride_l, summary_c, pattern, head_mode, b, h, d, dtype)
     if workspace is None:
+        need = sparse_attn_decode_workspace_size(pos, stride_l, summary_c, pattern, head_mode, b, h, d, dtype)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     qs = (ctypes.c_int64 * 2)(q.stride(0), q.stride(1))
     ks = (ctypes.c_int64 * 3)(k_cache.stride(0), k_cache.stride(1), k_cache.stride(2))
-    sparse_attn_decode(pos, stride_l, summary_c, pattern, head_mode, b, h, d, dtype, q, qs, k_cache, v_cache, ks,
-                       _scale(softmax_scale, d), o, lse, workspace, workspace.numel() * workspace.element_size(),
-                       stream)
+    try:
+        sparse_attn_decode(pos, stride_l, summary_c, pattern, head_mode, b, h, d, dtype, q, qs, k_cache, v_cache, ks,
+                           _scale(softmax_scale, d), o, lse, workspace, workspace.numel() * workspace.element_size(),
+                           stream)
+    except SparseAttnError:
+        # a pattern or shape that the size query refuses is reported by it, with or without a workspace
+        sparse_attn_decode_workspace_size(pos, stride_l, summary_c, pattern, head_mode, b, h, d, dtype)
+        raise
     return o, lse
 
 

@@ -27,12 +27,15 @@ namespace {
 constexpr int kCombineThreads = 256;
 constexpr int kKeysPerSplit = 256;    // target keys per workgroup
 constexpr int kMaxWorkgroups = 4096;  // splits are capped at this over all (batch, head)
-// Up to one workgroup per compute unit, sixteen waves walk a range instead of four:
-// such a step is bound by the latency of its serial passes over the range (four
-// waves take 32 rows of d = 64 a pass), and the chip has room for the waves.  With
-// the output written by the split kernel where there is one range: one text
-// sequence (223 keys, 8 heads of 64) 14.4 -> 11.5 us a step, the host's calls included.
-constexpr int kWideWorkgroups = 256;
+// Up to this many workgroups, sixteen waves walk a range instead of four: such a
+// step is bound by the latency of its serial passes over the range (four waves take
+// 32 rows of d = 64 a pass), and the chip has room for the waves.  Four against
+// sixteen, us a step on the device, d = 64: strided n = 12,288, l = 128, 8 workgroups
+// 6.1 | 5.1 (7.9 with a second launch for the one range), 256 9.4 | 7.7, 384 10.2 |
+// 9.3, 1,024 14.8 | 16.8; fixed n = 65,536, 264 12.2 | 10.5, 528 14.4 | 14.5; strided
+// n = 1,048,576, 128 13.1 | 9.7, 512 15.5 | 15.9; fp32, d = 128, 8 9.5 | 6.3, 512
+// 24.4 | 25.1.
+constexpr int kWideWorkgroups = 384;
 
 struct DecodeArgs {
     int pattern, mode, heads, splits;
@@ -217,7 +220,7 @@ decode_split_kernel(DecodeArgs a, const T* __restrict__ q, const T* __restrict__
 // of all ranges with one lane per range, then the D-wide sums are shared by
 // groups of D threads, each taking every G-th range, and added in group order
 // (one thread per element merging state by state: 93.3 -> 90.1 us for the whole
-// step at 16 ranges of 32 sequences, 8 heads of 64).
+// step at 16 ranges of 32 sequences, 8 heads of 64, 20.8 -> 12.2 at 33 ranges of one).
 template <int D, typename T>
 __global__ void __launch_bounds__(kCombineThreads)
 decode_combine_kernel(DecodeArgs a, const float* __restrict__ part, T* __restrict__ o, float* __restrict__ lse) {

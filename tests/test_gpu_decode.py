@@ -63,11 +63,11 @@ def test_decode_matches_oracle_rows(pattern, mode, n, l, c, d, dtype, batch, hea
 
 
 # Launch rules of a step: |S_pos| = 256 is one range (o and LSE written by the
-# split kernel), 257 two; up to 256 workgroups have sixteen waves each, more
+# split kernel), 257 two; up to 384 workgroups have sixteen waves each, more
 # have four; 2,100 keys in nine ranges do not divide among the combine's groups.
 @pytest.mark.parametrize("d,dtype,batch,heads,keys", [
-    (32, torch.float32, 2, 128, 256), (32, torch.float32, 1, 257, 256), (32, torch.bfloat16, 1, 128, 257),
-    (64, torch.bfloat16, 3, 43, 257), (64, torch.bfloat16, 1, 1, 2100), (128, torch.bfloat16, 2, 2, 2100),
+    (32, torch.float32, 2, 192, 256), (32, torch.float32, 1, 385, 256), (32, torch.bfloat16, 1, 192, 257),
+    (64, torch.bfloat16, 1, 193, 257), (64, torch.bfloat16, 1, 1, 2100), (128, torch.bfloat16, 2, 2, 2100),
     (128, torch.float32, 1, 2, 1), (64, torch.float32, 1, 2, 31),
 ])
 def test_decode_launch_rules(d, dtype, batch, heads, keys):

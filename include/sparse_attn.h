@@ -302,8 +302,8 @@ int sparse_attn_decode(int64_t pos, int32_t stride_l, int32_t summary_c, int32_t
  * part computed by transposition (Sec. 5.5: reordered by residue mod l, a
  * stride of l becomes a local window), with the caller choosing the class
  * block.  Same results as sparse_attn_fwd / sparse_attn_bwd over the merged
- * layout (which take this route by themselves for bf16 when l divides n, B
- * divides l and n / l is a multiple of 16), computed as
+ * layout (which take this route or a one-pass form of it by themselves for
+ * bf16 where it is faster), computed as
  *   the band  A1 = {max(0, i-l) .. i}: the block kernels over the strided A1
  *             layout (sparse_attn_layout with SA_MODE_A1 and the same n,
  *             block, stride_l, summary_c = 0), and

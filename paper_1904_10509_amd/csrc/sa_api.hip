@@ -202,21 +202,29 @@ struct StridedPlan {
 // Where those hold, one pass is used for the forward up to l = 128 (n = 12,288, 16
 // heads, l = 128: 49 against 56 us; l = 512: 81 against 70; n = 65,536, 8 heads, l =
 // 256: 190 against 160: its waves read the band's keys for 16 rows each, the band
-// kernel for 64) and never for the backward (137 against 135, l = 256 155 against
+// kernel for 64), for classes of up to 256 (l = 128, 4 heads, M = 512: 111 against 94) and
+// from 192 workgroups (d = 128: 32 24 against 13, 128 23.5 against 22.6, 192 30 against
+// 35; d = 64: 32 14 against 10, 256 18 against 24), and never for the backward (137 against 135, l = 256 155 against
 // 139).  Elsewhere the choice is between one pass and the block path, which
 // steps through every block that holds a pair: per multiple of l two blocks of a
 // row, every block when l < B, or one cheap diagonal when B divides l.  One pass
 // wins where those outnumber the band's blocks by kFarToBand (forward + backward,
 // 16 heads of 64, 2.4 times: n = 12,288, l = 111 1,379 -> 203 us; 1.5 to 2: n =
 // 1,024, l = 100 66 -> 47; 1.1: n = 4,096, l = 400 103 -> 113; 0.45: l = 600 107 ->
-// 161; diagonals, n = 3,072, l = 128, d = 128, 8 heads 108 -> 108).
+// 161; diagonals, n = 3,072, l = 128, d = 128, 8 heads 108 -> 108), and where a row
+// has enough of them: a short sequence's one pass is bound by the latency of its
+// phases, whatever n (d = 64 about 40 us, d = 128 82), and the block path by its
+// steps, the cheaper the smaller B (d = 128, 4 to 16 heads, block path | one pass: B =
+// 64, 3.3 steps a row 55 | 83, 5.3 74 | 82, 6.3 90 | 83; B = 32, 9 51 | 63; B = 16, 15 92
+// | 83; d = 64: B = 64, 3.3 38 | 40; B = 32, 3.5 31 | 37).
 //
 // A2 alone goes by classes from kMinFarBlocks block steps a row on average (n =
 // 8,192, l = 1,000 114 -> 54 us; n = 512, l = 128 44 -> 42), alternating heads, two
 // launches more, from kMinFarAlternate (n = 3,072, l = 128, d = 128 99 -> 52; n = 768,
 // l = 64 43 -> 50).
 constexpr double kFarToBand = 1.3, kMinFarBlocks = 4.0, kMinFarAlternate = 8.0;
-constexpr int32_t kFusedMinStride = 8, kFusedAlignedMaxStride = 128;
+constexpr int32_t kFusedMinStride = 8, kFusedAlignedMaxStride = 128, kFusedAlignedMaxClass = 256;
+constexpr int64_t kFusedAlignedMinTiles = 192;
 
 bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d, int32_t dtype,
                   const int64_t* strides, float scale, bool backward, StridedPlan* s) {
@@ -252,8 +260,11 @@ bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
     const double steps = p.l % p.block == 0 ? 0.35 : (p.l >= p.block ? 2.0 : (double)p.l / p.block);
     if (s->merge) {
         const bool aligned = p.n % p.l == 0 && p.l % p.block == 0 && M % 16 == 0;
-        const bool better = aligned ? !backward && p.l <= kFusedAlignedMaxStride
-                                    : 0.5 * (double)(M - 2) * steps >= kFarToBand * (sa::band_blocks(s->rows) + 1);
+        const double far = 0.5 * (double)(M - 2) * steps;
+        const bool better = aligned ? !backward && p.l <= kFusedAlignedMaxStride && M <= kFusedAlignedMaxClass &&
+                                              sa::strided_tiles(s->rows) >= kFusedAlignedMinTiles
+                                    : far >= kFarToBand * (sa::band_blocks(s->rows) + 1) &&
+                                          far >= (d == 128 ? 6.0 : 4.0) * (p.block == 64 ? 1.0 : p.block == 32 ? 1.6 : 2.5);
         s->fused = better && p.l >= kFusedMinStride && 64 * (int64_t)p.l * strides[2] < ((int64_t)1 << 32) &&
                    sa::strided_tiles(s->rows) < (1 << 22);
         if (s->fused) return true;

@@ -30,6 +30,8 @@ CASES = [
     (MG, 2000, 16, 3, 32, 1, 2),      # 666 or 667
     (MG, 3072, 64, 128, 128, 2, 2),   # 24
     (MG, 832, 64, 64, 64, 1, 2),      # 13: class blocks of 16
+    (MG, 1024, 64, 64, 64, 6, 8),     # 16: 192 workgroups of the one-pass forward, its smallest
+    (MG, 1024, 64, 64, 64, 1, 47),    # 188: band and classes apart
     (A2, 1008, 16, 50, 64, 1, 2),     # 20 or 21
     (A2, 1088, 64, 130, 64, 2, 2),    # 8 or 9
     (A2, 2000, 16, 7, 128, 1, 1),     # 285 or 286

@@ -197,31 +197,41 @@ struct StridedPlan {
 // Returns false where the block path over the layout stays: fp32; (batch, head)
 // strides that do not make one index; grids out of range; and the sizes below.
 //
-// Merged heads.  Band and class launches meet in bf16 and need classes that fill
-// their blocks (l | n, n / l a multiple of 16) and a band of whole blocks (B | l).
-// Where those hold, one pass is used for the forward up to l = 128 (n = 12,288, 16
+// Precision first.  With l a multiple of B the block path takes the blocks away from
+// the band, single diagonals, with fp32 probabilities and score gradients; the class
+// and one-pass kernels round both to bf16 (A2 alone, n = 2,560, l = 64: error of dV
+// 1.36 times the rounding of the result against 1.12, of dQ 1.61 against 1.32).  So
+// with B | l only classes that fill blocks of 16 or more, merged or A2 alone, go by
+// classes (n = 12,288, l = 128, 16 heads merged, backward: 135 us).  With any other l
+// the block path rounds them as well.
+//
+// Merged heads, B | l and filled classes: band and class launches, which meet in
+// bf16, or one pass.  One pass is used for the forward up to l = 128 (n = 12,288, 16
 // heads, l = 128: 49 against 56 us; l = 512: 81 against 70; n = 65,536, 8 heads, l =
 // 256: 190 against 160: its waves read the band's keys for 16 rows each, the band
-// kernel for 64), for classes of up to 256 (l = 128, 4 heads, M = 512: 111 against 94) and
-// from 192 workgroups (d = 128: 32 24 against 13, 128 23.5 against 22.6, 192 30 against
-// 35; d = 64: 32 14 against 10, 256 18 against 24), and never for the backward (137 against 135, l = 256 155 against
-// 139).  Elsewhere the choice is between one pass and the block path, which
-// steps through every block that holds a pair: per multiple of l two blocks of a
-// row, every block when l < B, or one cheap diagonal when B divides l.  One pass
-// wins where those outnumber the band's blocks by kFarToBand (forward + backward,
-// 16 heads of 64, 2.4 times: n = 12,288, l = 111 1,379 -> 203 us; 1.5 to 2: n =
-// 1,024, l = 100 66 -> 47; 1.1: n = 4,096, l = 400 103 -> 113; 0.45: l = 600 107 ->
-// 161; diagonals, n = 3,072, l = 128, d = 128, 8 heads 108 -> 108), and where a row
-// has enough of them: a short sequence's one pass is bound by the latency of its
-// phases, whatever n (d = 64 about 40 us, d = 128 82), and the block path by its
-// steps, the cheaper the smaller B (d = 128, 4 to 16 heads, block path | one pass: B =
-// 64, 3.3 steps a row 55 | 83, 5.3 74 | 82, 6.3 90 | 83; B = 32, 9 51 | 63; B = 16, 15 92
-// | 83; d = 64: B = 64, 3.3 38 | 40; B = 32, 3.5 31 | 37).
+// kernel for 64; between 128 and 256 nothing was measured), for classes of up to 256
+// (l = 128, 4 heads, M = 512: 111 against 94) and from 192 workgroups (d = 128: 32 24
+// against 13, 128 23.5 against 22.6, 192 30 against 35; d = 64: 32 14 against 10, 256
+// 18 against 24), and never for the backward (137 against 135, l = 256 155 against
+// 139).
 //
-// A2 alone goes by classes from kMinFarBlocks block steps a row on average (n =
-// 8,192, l = 1,000 114 -> 54 us; n = 512, l = 128 44 -> 42), alternating heads, two
-// launches more, from kMinFarAlternate (n = 3,072, l = 128, d = 128 99 -> 52; n = 768,
-// l = 64 43 -> 50).
+// Merged heads otherwise: one pass or the block path, which steps through every block
+// that holds a pair: per multiple of l two blocks of a row, or every block when l < B.
+// One pass wins where those outnumber the band's blocks by kFarToBand (forward +
+// backward, 16 heads of 64, 2.4 times: n = 12,288, l = 111 1,379 -> 203 us; 1.5 to 2: n
+// = 1,024, l = 100 66 -> 47; 1.1: n = 4,096, l = 400 103 -> 113; 0.45: l = 600 107 ->
+// 161; 8 heads, 3.6: n = 65,536, l = 1,000 2,719 -> 1,405), and where a row has enough
+// of them: a short sequence's one pass is bound by the latency of its phases, whatever
+// n (d = 64 about 40 us, d = 128 82), and the block path by its steps, the cheaper the
+// smaller B (d = 128, 4 to 16 heads, block path | one pass: B = 64, 3.3 steps a row 55
+// | 83, 5.3 74 | 82, 6.3 90 | 83; B = 32, 9 51 | 63; B = 16, 15 92 | 83; d = 64: B = 64,
+// 3.3 38 | 40; B = 32, 3.5 31 | 37).
+//
+// A2 alone, l no multiple of B, goes by classes from kMinFarBlocks block steps a row on
+// average (block path | classes, forward + backward, d = 64: n = 8,192, l = 1,000, 8.2
+// steps 72 | 34 us; n = 1,024, l = 24, 6 steps 67 | 12), alternating heads, two
+// launches more, from kMinFarAlternate (l = 1,000 116 | 90; n = 768, l = 50, 6.1 steps 55
+// | 27: the line is on the safe side).
 constexpr double kFarToBand = 1.3, kMinFarBlocks = 4.0, kMinFarAlternate = 8.0;
 constexpr int32_t kFusedMinStride = 8, kFusedAlignedMaxStride = 128, kFusedAlignedMaxClass = 256;
 constexpr int64_t kFusedAlignedMinTiles = 192;
@@ -256,10 +266,12 @@ bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
     if (!s->classes) return true;
     const int32_t first = alternate ? 1 : 0;
     s->rows = subset(class_heads, first);
-    // the block path's steps per multiple of l, a diagonal counted as a third
-    const double steps = p.l % p.block == 0 ? 0.35 : (p.l >= p.block ? 2.0 : (double)p.l / p.block);
+    // classes that fill blocks of 16 or more
+    const bool filled = p.n % p.l == 0 && M % 16 == 0;
+    if (p.l % p.block == 0 && (alternate || !filled)) return false;  // fp32 diagonals
+    const double steps = p.l >= p.block ? 2.0 : (double)p.l / p.block;  // the block path's, per multiple of l
     if (s->merge) {
-        const bool aligned = p.n % p.l == 0 && p.l % p.block == 0 && M % 16 == 0;
+        const bool aligned = filled && p.l % p.block == 0;
         const double far = 0.5 * (double)(M - 2) * steps;
         const bool better = aligned ? !backward && p.l <= kFusedAlignedMaxStride && M <= kFusedAlignedMaxClass &&
                                               sa::strided_tiles(s->rows) >= kFusedAlignedMinTiles
@@ -269,7 +281,7 @@ bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
                    sa::strided_tiles(s->rows) < (1 << 22);
         if (s->fused) return true;
         if (!aligned) return false;
-    } else if (0.5 * (double)M * (p.l % p.block == 0 ? 1.0 : steps) < (alternate ? kMinFarAlternate : kMinFarBlocks)) {
+    } else if (p.l % p.block != 0 && 0.5 * (double)M * steps < (alternate ? kMinFarAlternate : kMinFarBlocks)) {
         return false;
     }
     if (batch > 1 && (strides[0] != (int64_t)heads * strides[1] || (alternate && heads % 2 != 0))) return false;

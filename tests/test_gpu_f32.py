@@ -55,3 +55,26 @@ def test_f32_views_and_repeats():
     ref = orc_mod.backward(*oracle_inputs(x), pattern=F, mode=MG, l=l, c=c, scale=d ** -0.5)
     names = ("o", "lse", "dq", "dk", "dv")
     check_all("f32 [b, n, h, d] views", {name: to64(t) for name, t in zip(names, runs[0])}, ref, torch.float32, names=names)
+
+
+def test_f32_small_weights():
+    """Weights far below a row's largest to the precision of fp32: every key has a
+    coordinate of V of its own and an exact score 0, -8.25, -8.5, ..., so that each
+    element of O is one weight.  Bar: two exponentials of 1 ulp (a wave's maximum and
+    the row's), 1 for the reciprocal, a rounding each for the products and the sum:
+    4.5 * 2^-23."""
+    dev = device()
+    n = d = 64
+    score = -(8.0 + 0.25 * torch.arange(n, dtype=torch.float64))
+    score[0] = 0.0
+    q, k = torch.zeros(2, 1, 1, n, d)
+    q[..., 0] = 1.0
+    k[..., 0] = score.float()
+    v = torch.eye(n).reshape(1, 1, n, d)
+    lay = sa.build_layout(n, 16, n, 0, S, A1, device=dev)
+    o, _ = sa.forward(q.to(dev), k.to(dev), v.to(dev), lay, 1.0)
+    w = torch.tril(torch.exp(score).expand(n, n))
+    ref = w / w.sum(1, keepdim=True)
+    err = ((o[0, 0].cpu().double() - ref).abs() / ref.clamp_min(1e-300)).tril().max().item()
+    print(f"f32 small weights: relative error {err:.2e}", flush=True)
+    assert err <= 4.5 * 2.0 ** -23

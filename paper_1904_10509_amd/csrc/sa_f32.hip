@@ -18,7 +18,7 @@
 // global memory in 16-byte loads (each tile's rows are read by one wave only, so
 // LDS staging would add a pass), the next tile's ahead of this one's products.
 // Measured (forward + backward): strided n = 256, one head of 32: 736 -> 23 us;
-// fixed n = 2,048, l = 128, c = 32, four heads of 64: 7,213 -> 151 us, both against
+// fixed n = 2,048, l = 128, c = 32, four heads of 64: 7,213 -> 157 us, both against
 // one thread per row or column on the VALU, with smaller errors (8.0e-7 -> 4.2e-7 of
 // the largest gradient's norm).  Exponentials are expf: __expf, whose error grows
 // with its argument (weights of e^-24 off by 8e-7 against 2e-7), saves 4%.
@@ -107,6 +107,78 @@ struct ColOp {
                 for (int e = 0; e < V; ++e) acc[V * hb + e] = mfma_f32(x[t][hb][e], b[t], acc[V * hb + e]);
     }
 };
+
+// Infinities and NaN.  A pair that is not attended has b = 0 in the sums above, but 0
+// x infinity and 0 x NaN are NaN.  The walks take no notice (a test in every partly
+// attended tile cost registers, and with them a workgroup per compute unit); a wave
+// whose sums come out non-finite walks its tiles a second time, with each row's
+// products kept by the columns that attend it alone, so that such an element
+// reaches what attends it and nothing else.
+// acc[d][r] += sum over the tile's rows of tile[row][d] b[row][r] where (row, r) is
+// attended (mask: bit t, this lane's pair 4 g + t).
+template <int D>
+__device__ inline void accumulate_attended(const float* tile, int64_t ss, f32x4 b, uint32_t mask, f32x4* acc, int g,
+                                           int r) {
+    constexpr int V = F32<D>::V, HB = F32<D>::HB;
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+        typename F32<D>::vec x[HB];
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+            x[hb] = *reinterpret_cast<const typename F32<D>::vec*>(tile + (int64_t)(4 * g + t) * ss + 16 * V * hb + V * r);
+        const float bt = t == 0 ? b[0] : t == 1 ? b[1] : t == 2 ? b[2] : b[3];
+#pragma unroll 1
+        for (int row = 0; row < 4; ++row) {  // rows 4 row + t, one at a time
+            const bool on = (__shfl(mask, 16 * row + r) >> t) & 1u;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const f32x4 sum = mfma_f32(g == row ? x[hb][e] : 0.f, g == row ? bt : 0.f, acc[V * hb + e]);
+                    if (on) acc[V * hb + e] = sum;
+                    __builtin_amdgcn_sched_barrier(0);  // one sum in flight: registers
+                }
+        }
+    }
+}
+
+// x, as a value the compiler knows nothing about.  The second walk is to need no more
+// registers than the first: what it computes from opaque lane numbers stays inside it.
+__device__ inline int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// dot_tile of rows in memory, with no operand kept.
+template <int D>
+__device__ inline f32x4 dot_rows(const float* a, const float* b, int64_t ss, int g, int r) {
+    f32x4 c = zero4();
+    a += (int64_t)r * ss + 4 * g;
+    b += (int64_t)r * ss + 4 * g;
+#pragma unroll 1
+    for (int s = 0; s < F32<D>::KS; ++s) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(a + 16 * s), y = *reinterpret_cast<const f32x4*>(b + 16 * s);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) c = mfma_f32(x[t], y[t], c);
+    }
+    return c;
+}
+
+// Whether an element of a wave's sums is an infinity or a NaN (by its bits: the
+// build lets comparisons assume that there is none).
+template <int D>
+__device__ inline bool non_finite(const f32x4* acc) {
+    uint32_t top = 0;
+#pragma unroll
+    for (int db = 0; db < F32<D>::DB; ++db)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t v = __float_as_uint(acc[db][t]) & 0x7FFFFFFFu;
+            top = v > top ? v : top;
+        }
+    return __builtin_amdgcn_ballot_w64(top >= 0x7F800000u) != 0ull;
+}
 
 // A wave's partial result [16 rows][D] to LDS, rows at stride RS.
 template <int D>
@@ -237,6 +309,32 @@ __device__ inline void for_tiles(Next&& next, const float* pa, const float* pb, 
     }
 }
 
+// One tile of the online softmax: scores s to weights, the running state rescaled.
+template <int D>
+__device__ inline f32x4 softmax_step(const Tile& t, f32x4 s, float scale, float& m_run, float& l_run, f32x4* acc) {
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        s[x] = (t.mask >> x) & 1u ? s[x] * scale : -INFINITY;
+        mloc = fmaxf(mloc, s[x]);
+    }
+    const float m_new = fmaxf(m_run, max_over_g(mloc));
+    // rows with nothing attended so far keep m = -inf; 0 as reference gives p = 0
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = expf(m_run - m_ref);
+    float psum = 0.f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        s[x] = expf(s[x] - m_ref);
+        psum += s[x];
+    }
+    l_run = fmaf(l_run, alpha, psum);
+    m_run = m_new;
+#pragma unroll
+    for (int db = 0; db < F32<D>::DB; ++db) acc[db] *= alpha;
+    return s;
+}
+
 // Entries of row block qb and column block kb a walk visits (see WALK_*).
 __device__ inline void row_entries(const AttnArgs& a, const int32_t* row_ptr, int lay, int qb, int* e0, int* e1) {
     *e0 = a.walk == WALK_BAND ? max(0, qb - band_blocks(a)) : 0;
@@ -257,7 +355,7 @@ __device__ inline void col_entries(const AttnArgs& a, const int32_t* col_ptr, in
 
 // Forward.  grid: (16-row groups, heads, batch), longest rows first.
 template <int D>
-__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(4)))
 fwd_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
                const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
                float* __restrict__ o, float* __restrict__ lse) {
@@ -286,29 +384,22 @@ fwd_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* _
                             [&](const Tile& t, const RowOp<D>& kf, const RowOp<D>&) {
             ColOp<D> vt;
             vt.load(v + base + (int64_t)t.first * a.ss, a.ss, g, r);
-            f32x4 s = dot_tile<D>(kf, qf);  // key t.first + 4 g + t, query row0 + r
-            float mloc = -INFINITY;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                s[x] = (t.mask >> x) & 1u ? s[x] * a.scale : -INFINITY;
-                mloc = fmaxf(mloc, s[x]);
-            }
-            const float m_new = fmaxf(m_run, max_over_g(mloc));
-            // rows with nothing attended so far keep m = -inf; 0 as reference gives p = 0
-            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = expf(m_run - m_ref);
-            float psum = 0.f;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                s[x] = expf(s[x] - m_ref);
-                psum += s[x];
-            }
-            l_run = fmaf(l_run, alpha, psum);
-            m_run = m_new;
-#pragma unroll
-            for (int db = 0; db < C::DB; ++db) acc[db] *= alpha;
-            vt.accumulate(s, acc);
+            // key t.first + 4 g + t, query row0 + r
+            vt.accumulate(softmax_step<D>(t, dot_tile<D>(kf, qf), a.scale, m_run, l_run, acc), acc);
         });
+        if (non_finite<D>(acc)) {
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db) acc[db] = zero4();
+            m_run = -INFINITY;
+            l_run = 0.f;
+            walk.init(a, mp, col_idx, e0, e1, w);
+            for (Tile t = walk.rows(rl, i0, g); t.first >= 0; t = walk.rows(rl, i0, g)) {
+                const int gg = opaque(g), rr = opaque(r);
+                const int64_t at = base + (int64_t)t.first * a.ss;
+                const f32x4 s = dot_rows<D>(k + at, q + base + (int64_t)row0 * a.ss, a.ss, gg, rr);
+                accumulate_attended<D>(v + at, a.ss, softmax_step<D>(t, s, a.scale, m_run, l_run, acc), t.mask, acc, gg, rr);
+            }
+        }
         // combine the waves' states, in wave order
         l_run = sum_over_g(l_run);
         store_partial<D>(sO[w], acc, g, r);
@@ -352,6 +443,17 @@ fwd_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* _
         __syncthreads();  // LSE read by all its row's threads; the partials are free again
         if (tid % 32 == 0) *lrow = res;
     }
+}
+
+// Score gradients of a tile in the dQ kernel's view, zero where a pair is not attended.
+__device__ inline f32x4 score_grad(const Tile& t, f32x4 s, f32x4 dp, float scale, float L, float nd) {
+    f32x4 ds;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const float p = expf(fmaf(s[x], scale, -L));
+        ds[x] = (t.mask >> x) & 1u ? p * (dp[x] + nd) : 0.f;
+    }
+    return ds;
 }
 
 // Sums the waves' partials [16][D] in LDS into this thread's D / 32 elements.
@@ -414,14 +516,21 @@ bwd_dq_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t
             ColOp<D> kt;
             kt.load(k + base + (int64_t)t.first * a.ss, a.ss, g, r);
             const f32x4 s = dot_tile<D>(kf, qf), dp = dot_tile<D>(vf, of);
-            f32x4 ds;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float p = (t.mask >> x) & 1u ? expf(fmaf(s[x], a.scale, -L)) : 0.f;
-                ds[x] = p * (dp[x] + nd);
-            }
-            kt.accumulate(ds, acc);
+            kt.accumulate(score_grad(t, s, dp, a.scale, L, nd), acc);
         });
+        if (non_finite<D>(acc)) {
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db) acc[db] = zero4();
+            walk.init(a, mp, col_idx, e0, e1, w);
+            const int64_t own = base + (int64_t)row0 * a.ss;
+            for (Tile t = walk.rows(rl, i0, g); t.first >= 0; t = walk.rows(rl, i0, g)) {
+                const int gg = opaque(g), rr = opaque(r);
+                const int64_t at = base + (int64_t)t.first * a.ss;
+                const f32x4 s = dot_rows<D>(k + at, q + own, a.ss, gg, rr);
+                const f32x4 dp = dot_rows<D>(v + at, dout + own, a.ss, gg, rr);
+                accumulate_attended<D>(k + at, a.ss, score_grad(t, s, dp, a.scale, L, nd), t.mask, acc, gg, rr);
+            }
+        }
         store_partial<D>(sAcc[w], acc, g, r);
         __syncthreads();
         const int row = tid / 32, col = (tid % 32) * (D / 32);
@@ -431,6 +540,18 @@ bwd_dq_f32_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t
 #pragma unroll
         for (int c = 0; c < D / 32; ++c) drow[c] = (a.epilogue == EPI_ADD ? drow[c] : 0.f) + out[c] * a.scale;
         __syncthreads();
+    }
+}
+
+// Weights and score gradients of a tile in the dK / dV kernel's view, zero where a
+// pair is not attended.
+__device__ inline void weights(const Tile& t, f32x4 s, f32x4 dp, float scale, const float* L, const float* nd, f32x4* p,
+                               f32x4* ds) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const bool on = (t.mask >> x) & 1u;
+        (*p)[x] = on ? expf(fmaf(s[x], scale, -L[x])) : 0.f;
+        (*ds)[x] = on ? (*p)[x] * (dp[x] + nd[x]) : 0.f;
     }
 }
 
@@ -460,30 +581,47 @@ bwd_dkdv_f32_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int32
         for (int db = 0; db < C::DB; ++db) dkacc[db] = dvacc[db] = zero4();
         int e0, e1;
         col_entries(a, col_ptr, head_layout(a, h), j0 / a.block, &e0, &e1);
-        TileWalk walk;
-        walk.init(a, mp, row_idx, e0, e1, w);
-        for_tiles<D, true>([&] { return walk.cols(cl, j0, a.qshift, any_summary, g); }, q + base, dout + base, a.ss, g, r,
-                           [&](const Tile& t, const RowOp<D>& qf, const RowOp<D>& of) {
-            float L[4], nd[4];  // queries t.first + 4 g + x
+        auto load_stats = [&](const Tile& t, int g, float* L, float* nd) {
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
                 const int64_t si = stat_index(a, b, h, t.first + 4 * g + x);
                 L[x] = lse[si];
                 nd[x] = ndelta[si];
             }
+        };
+        TileWalk walk;
+        walk.init(a, mp, row_idx, e0, e1, w);
+        for_tiles<D, true>([&] { return walk.cols(cl, j0, a.qshift, any_summary, g); }, q + base, dout + base, a.ss, g, r,
+                           [&](const Tile& t, const RowOp<D>& qf, const RowOp<D>& of) {
+            float L[4], nd[4];  // queries t.first + 4 g + x
+            load_stats(t, g, L, nd);
             ColOp<D> ot, qt;
             ot.load(dout + base + (int64_t)t.first * a.ss, a.ss, g, r);
             const f32x4 s = dot_tile<D>(qf, kf), dp = dot_tile<D>(of, vf);
             qt.load(q + base + (int64_t)t.first * a.ss, a.ss, g, r);
             f32x4 p, ds;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                p[x] = (t.mask >> x) & 1u ? expf(fmaf(s[x], a.scale, -L[x])) : 0.f;
-                ds[x] = p[x] * (dp[x] + nd[x]);
-            }
+            weights(t, s, dp, a.scale, L, nd, &p, &ds);
             ot.accumulate(p, dvacc);
             qt.accumulate(ds, dkacc);
         });
+        if (non_finite<D>(dkacc) || non_finite<D>(dvacc)) {
+#pragma unroll
+            for (int db = 0; db < C::DB; ++db) dkacc[db] = dvacc[db] = zero4();
+            walk.init(a, mp, row_idx, e0, e1, w);
+            const int64_t own = base + (int64_t)j0 * a.ss;
+            for (Tile t = walk.cols(cl, j0, a.qshift, any_summary, g); t.first >= 0;
+                 t = walk.cols(cl, j0, a.qshift, any_summary, g)) {
+                const int gg = opaque(g), rr = opaque(r);
+                const int64_t at = base + (int64_t)t.first * a.ss;
+                float L[4], nd[4];
+                load_stats(t, gg, L, nd);
+                f32x4 p, ds;
+                weights(t, dot_rows<D>(q + at, k + own, a.ss, gg, rr), dot_rows<D>(dout + at, v + own, a.ss, gg, rr), a.scale,
+                        L, nd, &p, &ds);
+                accumulate_attended<D>(dout + at, a.ss, p, t.mask, dvacc, gg, rr);
+                accumulate_attended<D>(q + at, a.ss, ds, t.mask, dkacc, gg, rr);
+            }
+        }
         const int row = tid / 32, col = (tid % 32) * (D / 32);
         const int64_t at = base + (int64_t)(j0 + row) * a.ss + col;
         const bool add = a.epilogue == EPI_ADD;

@@ -109,6 +109,57 @@ __device__ inline void for_chunks(const Walk& w, const uint16_t* pa, const uint1
     }
 }
 
+// Infinities and NaN.  A pair that is not attended enters the products with weight
+// 0, but 0 x infinity and 0 x NaN are NaN, and a chunk reaches up to 31 rows past
+// the last attended one: 31 l positions in a class.  The chunks take no notice; a
+// workgroup whose sums come out non-finite runs a second time, with the products of
+// partly attended chunks kept by the rows that attend them alone, so that such an
+// element reaches what attends it and nothing else.
+// acc += the products of chunk rows 0 .. 31 (operands a, b, see pack_bf16x8) with this
+// lane's row, which attends the rows lo .. hi of the chunk.
+template <int DB>
+__device__ inline void accumulate_attended(const bf16x8* a, bf16x8 b, int lo, int hi, int g, f32x4* acc) {
+    const u32x4 bw = __builtin_bit_cast(u32x4, b);
+#pragma unroll 1
+    for (int x = 0; x < 32; ++x) {  // one row at a time
+        const int e = (x >> 4) * 4 + (x & 3);
+        u32x4 keep;
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+            keep[y] = g == ((x >> 2) & 3) && y == (e >> 1) ? ((e & 1) ? 0xFFFF0000u : 0xFFFFu) : 0u;
+        const bf16x8 bx = __builtin_bit_cast(bf16x8, bw & keep);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const bf16x8 ax = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, a[db]) & keep);
+            const f32x4 sum = mfma_16x16x32(ax, bx, acc[db]);
+            if (x >= lo && x <= hi) acc[db] = sum;
+            __builtin_amdgcn_sched_barrier(0);  // one sum in flight: registers
+        }
+    }
+}
+
+// x, as a value the compiler knows nothing about: what the second run computes from it
+// stays inside it and holds no registers in the first.
+__device__ inline int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Whether an element of the sums is an infinity or a NaN (by its bits: the build lets
+// comparisons assume that there is none).
+template <int N>
+__device__ inline bool non_finite(const f32x4* acc) {
+    uint32_t top = 0;
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const uint32_t v = __float_as_uint(acc[x][y]) & 0x7FFFFFFFu;
+            top = v > top ? v : top;
+        }
+    return top >= 0x7F800000u;
+}
+
 // Hands the units' accumulators (lane (g, r): row r, elements 16 db + 4 g + t) from
 // the band's rows to the classes' rows.  Uses all of LDS: barriers on both sides.
 template <int D, int W>
@@ -144,19 +195,24 @@ strided_fwd_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* _
     using C = SCfg<D, W>;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SShared<D, W, false>::kBytes];
     __shared__ float sM[16][17], sL[16][17];  // [unit][row]
+    __shared__ uint32_t sBad;
     STile t;
     if (!strided_tile(a, blockIdx.x, &t)) return;
-    const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
+    const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int64_t base = head_base(a, t.b, t.h);
     const uint16_t* tK = reinterpret_cast<const uint16_t*>(smem + w * SShared<D, W, false>::kWave);
     const uint16_t* tV = tK + C::TILE;
-    TileReader<D> rd;
-    rd.init(g, r);
     const float c2 = a.scale_log2;
 
     f32x4 acc[SCfg<D, W>::UNITS][C::DB];
     float m_run[SCfg<D, W>::UNITS], l_run[SCfg<D, W>::UNITS];
+    if (tid == 0) sBad = 0;
+    auto run = [&](auto again) {
+    constexpr bool kAgain = decltype(again)::value;
+    const int lane = kAgain ? opaque(tid % 64) : tid % 64, g = lane / 16, r = lane % 16;
+    TileReader<D> rd;
+    rd.init(g, r);
     auto unit = [&](bool cls, int uu) {
         const Walk wk = query_walk(a, t, cls, w + C::NW * uu, r);
         if (!wk.on) return;
@@ -204,6 +260,12 @@ strided_fwd_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* _
             const float alpha = exp2_fast((m_run[uu] - m_ref) * c2);
             l_run[uu] = fmaf(l_run[uu], alpha, psum);
             m_run[uu] = m_new;
+            if constexpr (kAgain) {
+#pragma unroll
+                for (int db = 0; db < C::DB; ++db) acc[uu][db] *= alpha;
+                accumulate_attended<C::DB>(vt, pf, full ? 0 : wk.lo - 32 * c, full ? 31 : wk.hi - 32 * c, g, acc[uu]);
+                return;
+            }
 #pragma unroll
             for (int db = 0; db < C::DB; ++db) acc[uu][db] = mfma_16x16x32(vt[db], pf, acc[uu][db] * alpha);
         });
@@ -240,6 +302,11 @@ strided_fwd_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* _
             lse[stat_index(a, t.b, t.h, wk.stat + (int64_t)(wk.own + r) * wk.stat_stride)] =
                 l_tot > 0.f ? m_run[uu] * a.scale + __logf(l_tot) : -INFINITY;
     }
+    };
+    run(std::false_type{});
+    if (non_finite<C::UNITS * C::DB>(&acc[0][0])) sBad = 1;
+    __syncthreads();
+    if (sBad) run(std::true_type{});
 }
 
 // dQ.  With a.row_stats it also forms its rows' -D_i = -dO_i . O_i and -LSE_i
@@ -253,18 +320,23 @@ strided_dq_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* __
     using C = SCfg<D, W>;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SShared<D, W, false>::kBytes];
     __shared__ float sD[16][17], sN[16][17];  // -D and -LSE log2 e, [unit][row]
+    __shared__ uint32_t sBad;
     STile t;
     if (!strided_tile(a, blockIdx.x, &t)) return;
-    const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
+    const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int64_t base = head_base(a, t.b, t.h);
     const uint16_t* tK = reinterpret_cast<const uint16_t*>(smem + w * SShared<D, W, false>::kWave);
     const uint16_t* tV = tK + C::TILE;
-    TileReader<D> rd;
-    rd.init(g, r);
     const float c2 = a.scale_log2;
 
     f32x4 acc[SCfg<D, W>::UNITS][C::DB];
+    if (tid == 0) sBad = 0;
+    auto run = [&](auto again) {
+    constexpr bool kAgain = decltype(again)::value;
+    const int lane = kAgain ? opaque(tid % 64) : tid % 64, g = lane / 16, r = lane % 16;
+    TileReader<D> rd;
+    rd.init(g, r);
     auto unit = [&](bool cls, int uu) {
         const int u = w + C::NW * uu;
         const Walk wk = query_walk(a, t, cls, u, r);
@@ -324,6 +396,12 @@ strided_dq_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* __
             if (!full) mask_pairs(s, chunk_mask(wk, c, g));
             s[0] *= dp[0];
             s[1] *= dp[1];
+            if constexpr (kAgain) {
+                if (!full) mask_pairs(s, chunk_mask(wk, c, g));
+                accumulate_attended<C::DB>(kt, pack_bf16x8(s[0], s[1]), full ? 0 : wk.lo - 32 * c,
+                                           full ? 31 : wk.hi - 32 * c, g, acc[uu]);
+                return;
+            }
             const bf16x8 dsf = pack_bf16x8(s[0], s[1]);
 #pragma unroll
             for (int db = 0; db < C::DB; ++db) acc[uu][db] = mfma_16x16x32(kt[db], dsf, acc[uu][db]);
@@ -346,6 +424,11 @@ strided_dq_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* __
         for (int db = 0; db < C::DB; ++db)
             *reinterpret_cast<uint2*>(drow + db * 16 + 4 * g) = pack_bf16x4_bits(acc[uu][db] * a.scale);
     }
+    };
+    run(std::false_type{});
+    if (non_finite<C::UNITS * C::DB>(&acc[0][0])) sBad = 1;
+    __syncthreads();
+    if (sBad) run(std::true_type{});
 }
 
 template <int D, int W>
@@ -356,23 +439,28 @@ strided_dkdv_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* 
                     uint16_t* __restrict__ dv) {
     using C = SCfg<D, W>;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SShared<D, W, true>::kBytes];
+    __shared__ uint32_t sBad[2];
     STile t;
     if (!strided_tile(a, blockIdx.x, &t)) return;
-    const int tid = threadIdx.x, lane = tid % 64, g = lane / 16, r = lane % 16;
+    const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid / 64);
     const int64_t base = head_base(a, t.b, t.h);
     const uint16_t* tQ = reinterpret_cast<const uint16_t*>(smem + w * SShared<D, W, true>::kWave);
     const uint16_t* tO = tQ + C::TILE;
     float* tS = reinterpret_cast<float*>(smem + w * SShared<D, W, true>::kWave + 4 * C::TILE);  // a chunk's -LSE log2 e, then -D
-    TileReader<D> rd;
-    rd.init(g, r);
     const float c2 = a.scale_log2;
 
     // At d = 128 dV and dK take a round each (S formed twice): accumulators of
     // both do not fit the registers.
+    if (tid < 2) sBad[tid] = 0;
     auto round = [&](auto which) {
     constexpr bool kV = decltype(which)::value != 2, kK = decltype(which)::value != 1;
     f32x4 dvacc[SCfg<D, W>::UNITS][C::DB], dkacc[SCfg<D, W>::UNITS][C::DB];
+    auto run = [&](auto again) {
+    constexpr bool kAgain = decltype(again)::value;
+    const int lane = kAgain ? opaque(tid % 64) : tid % 64, g = lane / 16, r = lane % 16;
+    TileReader<D> rd;
+    rd.init(g, r);
     auto unit = [&](bool cls, int uu) {
         const Walk wk = key_walk(a, t, cls, w + C::NW * uu, r);
         if (!wk.on || wk.count <= 0) return;
@@ -403,12 +491,17 @@ strided_dkdv_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* 
             nl[0] = *reinterpret_cast<const f32x4*>(tS + 4 * g);
             nl[1] = *reinterpret_cast<const f32x4*>(tS + 16 + 4 * g);
             bf16x8 ot[C::DB], qt[C::DB];
+            auto read = [&](bool o, bool q) {
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db) {
-                if constexpr (kV) ot[db] = rd.tr(tO, 0, 16, db);
-                if constexpr (kK) qt[db] = rd.tr(tQ, 0, 16, db);
+                for (int db = 0; db < C::DB; ++db) {
+                    if (o) ot[db] = rd.tr(tO, 0, 16, db);
+                    if (q) qt[db] = rd.tr(tQ, 0, 16, db);
+                }
+            };
+            if constexpr (!kAgain) {
+                read(kV, kK);
+                next();
             }
-            next();
             st = stat(c + 1);  // (clamped to the last row past the end)
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -418,6 +511,20 @@ strided_dkdv_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* 
             if constexpr (kK) {
                 ds[0] *= p[0];
                 ds[1] *= p[1];
+            }
+            if constexpr (kAgain) {
+                const int lo = full ? 0 : wk.lo - 32 * c, hi = full ? 31 : wk.hi - 32 * c;
+                if constexpr (kV) {
+                    read(true, false);
+                    accumulate_attended<C::DB>(ot, pack_bf16x8(p[0], p[1]), lo, hi, g, dvacc[uu]);
+                }
+                if constexpr (kK) {
+                    read(false, true);
+                    if (!full) mask_pairs(ds, chunk_mask(wk, c, g));
+                    accumulate_attended<C::DB>(qt, pack_bf16x8(ds[0], ds[1]), lo, hi, g, dkacc[uu]);
+                }
+                next();
+                return;
             }
             if constexpr (kV) {
                 const bf16x8 pb = pack_bf16x8(p[0], p[1]);
@@ -455,6 +562,12 @@ strided_dkdv_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* 
                 *reinterpret_cast<uint2*>(dk + at + db * 16 + 4 * g) = pack_bf16x4_bits(dkacc[uu][db] * a.scale);
         }
     }
+    };
+    run(std::false_type{});
+    uint32_t* const bad = &sBad[kV ? 0 : 1];
+    if ((kV && non_finite<C::UNITS * C::DB>(&dvacc[0][0])) || (kK && non_finite<C::UNITS * C::DB>(&dkacc[0][0]))) *bad = 1;
+    __syncthreads();
+    if (*bad) run(std::true_type{});
     };
     if constexpr (D == 128) {
         round(std::integral_constant<int, 1>{});

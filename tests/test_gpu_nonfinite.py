@@ -42,7 +42,7 @@ def poisoned(x, names, at, value):
     return out
 
 
-def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value):
+def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value, backward=True):
     dev = device()
     x = make_inputs(batch, heads, n, d, dtype, seed=n + l + d)
     scale = d ** -0.5
@@ -53,24 +53,26 @@ def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value):
     keys = {name: t.to(dev) for name, t in poisoned(x, ("k", "v"), at, value).items()}
     rows = {name: t.to(dev) for name, t in poisoned(x, ("q", "dout"), at, value).items()}
     o1, lse1 = sa.forward(keys["q"], keys["k"], keys["v"], lay, scale)
-    dq1, _, _ = sa.backward(keys["q"], keys["k"], keys["v"], o, keys["dout"], lse, lay, scale)
-    dq2, dk2, dv2 = sa.backward(rows["q"], rows["k"], rows["v"], o, rows["dout"], lse, lay, scale)
+    grads1 = grads2 = None
+    if backward:
+        grads1 = sa.backward(keys["q"], keys["k"], keys["v"], o, keys["dout"], lse, lay, scale)
+        grads2 = sa.backward(rows["q"], rows["k"], rows["v"], o, rows["dout"], lse, lay, scale)
     torch.cuda.synchronize()
     for h in range(heads):
         own = attended(pattern, mode, n, l, c, h)
-        free = ~own[:, at]                # rows that attend no poisoned key
-        far = ~own[at].any(axis=0)        # keys that no poisoned row attends
-        free, far = free.all(axis=1) if free.ndim > 1 else free, far
-        other = np.ones(n, dtype=bool)
-        other[at] = False
+        free = ~own[:, at].any(axis=1)  # rows that attend no poisoned key
+        far = ~own[at].any(axis=0)      # keys that no poisoned row attends
+        other = ~np.isin(np.arange(n), at)
         label = f"{value} at {at} p{pattern} m{mode} n{n} B{B} l{l} d{d} head {h}"
         pick = lambda t, keep: to64(t)[:, h][:, keep]  # noqa: E731
         check(f"{label} o", pick(o1, free), ref["o"][:, h][:, free], dtype)
         check_lse(f"{label} lse", pick(lse1, free), ref["lse"][:, h][:, free], dtype)
-        check(f"{label} dq (keys)", pick(dq1, free), ref["dq"][:, h][:, free], dtype)
-        check(f"{label} dq (rows)", pick(dq2, other), ref["dq"][:, h][:, other], dtype)
-        check(f"{label} dk", pick(dk2, far), ref["dk"][:, h][:, far], dtype)
-        check(f"{label} dv", pick(dv2, far), ref["dv"][:, h][:, far], dtype)
+        if not backward:
+            continue
+        check(f"{label} dq (keys)", pick(grads1[0], free), ref["dq"][:, h][:, free], dtype)
+        check(f"{label} dq (rows)", pick(grads2[0], other), ref["dq"][:, h][:, other], dtype)
+        check(f"{label} dk", pick(grads2[1], far), ref["dk"][:, h][:, far], dtype)
+        check(f"{label} dv", pick(grads2[2], far), ref["dv"][:, h][:, far], dtype)
 
 
 # (pattern, mode, n, B, l, c, d, heads, poisoned positions)
@@ -85,3 +87,17 @@ def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value):
 ])
 def test_f32(pattern, mode, n, B, l, c, d, heads, at, value):
     run_poisoned(pattern, mode, n, B, l, c, d, torch.float32, 1, heads, at, value)
+
+
+# the one-pass kernels: a chunk reaches up to 31 rows, in a class 31 l positions, past
+# the last attended one
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n,B,l,d,batch,heads,at", [
+    (1024, 64, 37, 64, 2, 2, [700, 41]),
+    (1536, 32, 47, 128, 1, 2, [1000, 1535]),
+    (1600, 64, 49, 32, 1, 1, [3, 900]),
+    (3072, 64, 24, 64, 1, 1, [2047]),
+    (1024, 64, 64, 64, 6, 8, [600]),    # filled classes: one pass in the forward alone
+])
+def test_one_pass(n, B, l, d, batch, heads, at, value):
+    run_poisoned(S, MG, n, B, l, 0, d, torch.bfloat16, batch, heads, at, value, backward=l % B != 0)

@@ -47,6 +47,11 @@
  *     at the sequence stride must span less than 4 GiB (2 * block * stride
  *     < 2^32 bytes), else SA_ERR_UNSUPPORTED.  LSE is [batch, heads, n]
  *     contiguous fp32 (natural logarithm).
+ *   - Inputs are meant to be finite.  An infinity or a NaN makes the results
+ *     that depend on it unspecified.  Results that do not depend on it stay
+ *     as they are in fp32; in bf16 the block kernels also multiply (by zero)
+ *     the other pairs of a 16 x 32 chunk that holds an attended one, so that
+ *     rows of the same block can become NaN.
  */
 #ifndef SPARSE_ATTN_H
 #define SPARSE_ATTN_H

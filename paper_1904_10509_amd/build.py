@@ -21,7 +21,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed fp32 VALU instructions are kept out of generated code on purpose.
 # MFMA results stay in ordinary VGPRs (the softmax works on them directly),
 # and maxima skip NaN quieting: the kernels never produce NaNs from finite
-# inputs, and inputs must be finite.
+# inputs, and what attends an infinity or a NaN is unspecified (tests for one
+# look at the bits: csrc/sa_finite.h).
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans",

@@ -44,6 +44,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "sa_finite.h"
 #include "sa_internal.h"
 #include "sa_mask.h"
 #include "sa_mfma.h"
@@ -763,6 +764,13 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                     dqacc[u][db] += red[(((x * C::RN + w) * C::QBW + u) * C::DB + db) * 64 + lane];
     }
 
+    if constexpr (kPadded && !WIDE) {
+        if (a.walk == WALK_DENSE && __builtin_amdgcn_ballot_w64(non_finite<C::DB>(dqacc[0])) != 0ull) {
+            class_dq_again<D>(a, rows, row0, q + base, k + base, v + base, dout + base, nl2[0], nd4[0][0], dq + base);
+            return;
+        }
+    }
+
     // this lane holds dQ^T at d = 16 db + 4g + t for query row0 + 16u + r
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {
@@ -1426,10 +1434,21 @@ bwd_dkdv_bf16_kernel(AttnArgs a, const int32_t* __restrict__ col_ptr, const int3
                     }
             }
         }
+        bool stored = false;
+        if constexpr (kPadded) {
+            if (a.walk == WALK_DENSE && len > 0 &&
+                __builtin_amdgcn_ballot_w64(non_finite<C::DB>(dvacc[0]) || non_finite<C::DB>(dkacc[0])) != 0ull) {
+                const int64_t st0 = stat_index(a, b, h, 0);
+                class_dkdv_again<D>(a, rows, kb * BLK + 16 * w, q + base, k + base, v + base, dout + base, nlse2 + st0,
+                                    ndelta + st0, dk + base, dv + base);
+                stored = true;
+            }
+        }
         // this lane holds dV^T / dK^T at d = 16 db + 4g + t for key key_of(kbw)
 #pragma unroll
         for (int kbw = 0; kbw < C::KBW; ++kbw) {
             if (PH > 1 && phase > 0) break;  // summed into phase 0
+            if (stored) break;
             if (single && qhalf == 1) break;  // written by the wave of the other query half
             const int j = key_of(kbw);
             if (kPadded && j >= rows) continue;
@@ -1813,8 +1832,12 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
         *reinterpret_cast<uint2*>(&sST[j * C::MP + 32 * qc + 4 * g]) = pack_bf16x4_bits(ds[0]);
         *reinterpret_cast<uint2*>(&sST[j * C::MP + 32 * qc + 16 + 4 * g]) = pack_bf16x4_bits(ds[1]);
     }
-    // this lane holds dV^T / dK^T at d = 16 db + 4 g + t for key j
-    if (j < rows) {
+    if (__builtin_amdgcn_ballot_w64(non_finite<C::DB>(dvacc) || non_finite<C::DB>(dkacc)) != 0ull) {
+        const int64_t st0 = stat_index(a, b, h, 0);
+        class_dkdv_again<D>(a, rows, 16 * w, q + base, k + base, v + base, dout + base, nlse2 + st0, ndelta + st0, dk + base,
+                            dv + base);
+    } else if (j < rows) {
+        // this lane holds dV^T / dK^T at d = 16 db + 4 g + t for key j
         uint16_t* dvrow = dv + base + (int64_t)j * a.ss;
         uint16_t* dkrow = dk + base + (int64_t)j * a.ss;
 #pragma unroll
@@ -1851,6 +1874,10 @@ bwd_class_bf16_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t
             if (db + 1 < C::DB) kT[(db + 1) & 1] = rd.tr(sK, 32 * kc, 32 * kc + 16, db + 1);
             dqacc[db] = mfma_16x16x32(kT[db & 1], dsb, dqacc[db]);
         }
+    }
+    if (__builtin_amdgcn_ballot_w64(non_finite<C::DB>(dqacc)) != 0ull) {
+        class_dq_again<D>(a, rows, q0, q + base, k + base, v + base, dout + base, sL[q0 + r], sD[q0 + r], dq + base);
+        return;
     }
     if (q0 + r >= rows) return;
     uint16_t* drow = dq + base + (int64_t)(q0 + r) * a.ss;

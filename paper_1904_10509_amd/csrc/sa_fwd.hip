@@ -13,6 +13,7 @@
 // per lane plus a two-step exchange over the four lane groups.
 //
 // fp32 path: sa_f32.hip.
+#include "sa_finite.h"
 #include "sa_internal.h"
 #include "sa_mask.h"
 #include "sa_mfma.h"
@@ -382,6 +383,13 @@ fwd_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_t* 
         cur = nxt;
         return true;
     });
+
+    if constexpr (kPadded && !WIDE) {
+        if (a.walk == WALK_DENSE && __builtin_amdgcn_ballot_w64(non_finite<C::DB>(oacc[0])) != 0ull) {
+            class_forward_again<D>(a, rows, row0, q + base, k + base, v + base, o + base, lse + stat_index(a, b, h, 0));
+            return;
+        }
+    }
 
 #pragma unroll
     for (int u = 0; u < C::QBW; ++u) {

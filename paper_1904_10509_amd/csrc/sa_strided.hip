@@ -27,6 +27,7 @@
 // and those of one head their class rows, so each XCD takes a consecutive range
 // of them.
 #include "sa_bwd_kernels.h"
+#include "sa_finite.h"
 #include "sa_strided.h"
 
 namespace sa {
@@ -107,57 +108,6 @@ __device__ inline void for_chunks(const Walk& w, const uint16_t* pa, const uint1
             if (c + 1 < chunks) load(c + 1);
         });
     }
-}
-
-// Infinities and NaN.  A pair that is not attended enters the products with weight
-// 0, but 0 x infinity and 0 x NaN are NaN, and a chunk reaches up to 31 rows past
-// the last attended one: 31 l positions in a class.  The chunks take no notice; a
-// workgroup whose sums come out non-finite runs a second time, with the products of
-// partly attended chunks kept by the rows that attend them alone, so that such an
-// element reaches what attends it and nothing else.
-// acc += the products of chunk rows 0 .. 31 (operands a, b, see pack_bf16x8) with this
-// lane's row, which attends the rows lo .. hi of the chunk.
-template <int DB>
-__device__ inline void accumulate_attended(const bf16x8* a, bf16x8 b, int lo, int hi, int g, f32x4* acc) {
-    const u32x4 bw = __builtin_bit_cast(u32x4, b);
-#pragma unroll 1
-    for (int x = 0; x < 32; ++x) {  // one row at a time
-        const int e = (x >> 4) * 4 + (x & 3);
-        u32x4 keep;
-#pragma unroll
-        for (int y = 0; y < 4; ++y)
-            keep[y] = g == ((x >> 2) & 3) && y == (e >> 1) ? ((e & 1) ? 0xFFFF0000u : 0xFFFFu) : 0u;
-        const bf16x8 bx = __builtin_bit_cast(bf16x8, bw & keep);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            const bf16x8 ax = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, a[db]) & keep);
-            const f32x4 sum = mfma_16x16x32(ax, bx, acc[db]);
-            if (x >= lo && x <= hi) acc[db] = sum;
-            __builtin_amdgcn_sched_barrier(0);  // one sum in flight: registers
-        }
-    }
-}
-
-// x, as a value the compiler knows nothing about: what the second run computes from it
-// stays inside it and holds no registers in the first.
-__device__ inline int opaque(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
-// Whether an element of the sums is an infinity or a NaN (by its bits: the build lets
-// comparisons assume that there is none).
-template <int N>
-__device__ inline bool non_finite(const f32x4* acc) {
-    uint32_t top = 0;
-#pragma unroll
-    for (int x = 0; x < N; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const uint32_t v = __float_as_uint(acc[x][y]) & 0x7FFFFFFFu;
-            top = v > top ? v : top;
-        }
-    return top >= 0x7F800000u;
 }
 
 // Hands the units' accumulators (lane (g, r): row r, elements 16 db + 4 g + t) from

@@ -42,7 +42,7 @@ def poisoned(x, names, at, value):
     return out
 
 
-def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value, backward=True):
+def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value, backward=True, only=None):
     dev = device()
     x = make_inputs(batch, heads, n, d, dtype, seed=n + l + d)
     scale = d ** -0.5
@@ -59,6 +59,8 @@ def run_poisoned(pattern, mode, n, B, l, c, d, dtype, batch, heads, at, value, b
         grads2 = sa.backward(rows["q"], rows["k"], rows["v"], o, rows["dout"], lse, lay, scale)
     torch.cuda.synchronize()
     for h in range(heads):
+        if only is not None and mode == IL and (A1, A2)[h % 2] != only:
+            continue  # (the band's blocks multiply a block's neighbours too)
         own = attended(pattern, mode, n, l, c, h)
         free = ~own[:, at].any(axis=1)  # rows that attend no poisoned key
         far = ~own[at].any(axis=0)      # keys that no poisoned row attends
@@ -101,3 +103,19 @@ def test_f32(pattern, mode, n, B, l, c, d, heads, at, value):
 ])
 def test_one_pass(n, B, l, d, batch, heads, at, value):
     run_poisoned(S, MG, n, B, l, 0, d, torch.bfloat16, batch, heads, at, value, backward=l % B != 0)
+
+
+# the residue classes (A2 alone, the odd ones of alternating heads): one launch per
+# class, separate launches, padded and whole class blocks
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("mode,n,B,l,d,heads,at", [
+    (A2, 1008, 16, 50, 64, 2, [600, 20]),
+    (A2, 1088, 64, 130, 32, 1, [700]),
+    (A2, 2000, 16, 7, 128, 1, [1000]),
+    (A2, 4096, 32, 32, 64, 1, [2000, 4095]),
+    (A2, 4112, 16, 12, 64, 1, [1999]),
+    (IL, 992, 32, 45, 64, 4, [500]),
+    (IL, 1280, 64, 30, 128, 2, [700]),
+])
+def test_classes(mode, n, B, l, d, heads, at, value):
+    run_poisoned(S, mode, n, B, l, 0, d, torch.bfloat16, 1, heads, at, value, only=A2)

@@ -1548,23 +1548,6 @@ inline bool split_products(const AttnArgs& a) {
     return w > 0.15;
 }
 
-// Whether four waves share each row's (dQ) and each key group's (dK / dV) walk, in
-// the fixed pattern with B < 64.  There only the c / l summary columns of a head are
-// long, and a workgroup of one or two waves walks each alone.  The rings of four
-// phases take a compute unit's LDS at d = 128, B = 32 (one workgroup), half of it or
-// less at smaller sizes, so this pays only while the long columns are few: up to
-// kPhaseColumns, a third of it at d = 128, B = 32.  Backward before and after: 8 heads
-// of 128, n = 3,072, l = 128, c = 32, B = 32 114 -> 94 us (192 columns), 12 heads 117 ->
-// 127 (288); d = 64, n = 20,000, 4 heads 1,017 -> 849 (568), n = 8,384, 32 heads 346 ->
-// 586 (2,080); d = 128, B = 16, n = 4,096, l = 64, c = 8, 4 heads 402 -> 160.
-constexpr int64_t kPhaseColumns = 600;
-inline bool walk_phases(const AttnArgs& a) {
-    if (a.pattern != FIXED || a.mode == MODE_A1) return false;
-    const int64_t heads = a.mode == MODE_INTERLEAVED ? a.heads / 2 : a.heads;
-    const int64_t columns = a.batch * heads * ((int64_t)a.n / a.l) * ((a.c + a.block - 1) / a.block);
-    return columns <= (a.d * a.block > 2048 ? kPhaseColumns / 3 : kPhaseColumns);
-}
-
 template <int D, int BLK>
 hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, const void* v,
                            const void* o, const void* dout, const float* lse, void* dq, void* dk,
@@ -1583,7 +1566,7 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
     return with_pattern_mode(a.pattern, a.mode, [&](auto pat, auto mode) {
         constexpr int PAT = decltype(pat)::value, MODE = decltype(mode)::value;
         constexpr int PHASES = PAT == FIXED && BLK < 64 && MODE != MODE_A1 ? 4 : 1;
-        const bool phases = PHASES > 1 && walk_phases(a);
+        const bool phases = PHASES > 1 && walk_phases(a, true), row_phases = PHASES > 1 && walk_phases(a, false);
         const int64_t slots =
             phases ? (split ? resident_workgroups<bwd_dkdv_bf16_kernel<D, BLK, PAT, MODE, PAT == FIXED, PHASES>>(
                                   DkvCfg<D, BLK, PAT, PHASES>::NT)
@@ -1654,7 +1637,7 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
                     if (wide_rows(a)) return dq_launch(sp, std::true_type{}, std::integral_constant<int, 1>{});
                 }
                 if constexpr (PHASES > 1) {
-                    if (phases) return dq_launch(sp, std::false_type{}, std::integral_constant<int, PHASES>{});
+                    if (row_phases) return dq_launch(sp, std::false_type{}, std::integral_constant<int, PHASES>{});
                 }
                 dq_launch(sp, std::false_type{}, std::integral_constant<int, 1>{});
             };

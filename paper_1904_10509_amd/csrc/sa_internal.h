@@ -124,6 +124,65 @@ inline bool wide_rows(const AttnArgs& a) {
     return (int64_t)a.batch * a.heads * ((a.nq + 1) / 2) >= kWideGroups;
 }
 
+// Block steps of the fixed pattern's walks, from its sizes alone: every step of a call,
+// and the longest walk of a row block and of a key block.  (Per (batch, head) nq walks;
+// those of far blocks, which hold summary keys, reach half the sequence on average,
+// those inside an l-block half of it.)
+struct WalkEstimate {
+    double steps, longest_row, longest_column;
+};
+inline WalkEstimate walk_estimate(const AttnArgs& a) {
+    const int32_t a2_heads = a.mode == MODE_INTERLEAVED ? a.heads / 2 : a.mode == MODE_A1 ? 0 : a.heads;
+    const int32_t a1_heads = a.mode == MODE_MERGED ? a.heads : a.heads - a2_heads;
+    const double nq = a.nq;
+    auto least = [&](double x) { return x < nq ? x : nq; };
+    const double far = a2_heads == 0 || a.n <= a.l - a.c
+                           ? 0.0
+                           : least((double)((a.n - 1) / a.l + 1) * ((a.c - 1) / a.block + 1));
+    const double local = a1_heads == 0 ? 0.0 : least((a.l - 1) / a.block + 1);
+    const double column = far > 0.0 ? nq - (a.l - a.c) / a.block : 0.0;
+    WalkEstimate w;
+    w.steps = 0.5 * nq * a.batch * (a2_heads * far + a1_heads * (local + 1.0));
+    w.longest_row = a.mode == MODE_MERGED ? far + local : far > local ? far : local;
+    w.longest_column = column > local ? column : local;
+    return w;
+}
+
+// Whether four waves share each row's (dQ) or each key group's (dK / dV) walk, in the
+// fixed pattern with B < 64.  A workgroup of one or two waves walks a row or column
+// alone, and the longest (a summary column: every block below it) sets the time while
+// all walks together do not fill the chip.  Four phases make it a quarter as long, but
+// their rings leave a compute unit one to four workgroups, whose waves wait for each
+// other at every step: with the chip full they take up to 2.4 times as long.  So the
+// line is on the work per compute unit in units of the longest walk: all block steps,
+// and kWalkSteps more for each walk (its own rows, the sum of the phases), over 256 times
+// the longest walk's steps.  dQ's line lies further out.  Measured on either side of
+// the lines (work: us without | with phases; l = 128 or as given, c = 32, merged):
+//   d = 128, B = 32, one workgroup per compute unit: dQ n = 3,072, 4 heads 2.1: 27 | 26; l =
+//     512, n = 2,048, 8 heads 3.5: 21 | 24; dK / dV l = 1,024, n = 4,096, 8 heads 1.8: 84 | 64;
+//     A2 alone, l = 256, n = 1,024, 16 heads 2.1: 28 | 35; l = 2 n, 16 heads 3.5: 60 | 85;
+//     two heads of l = n = 11,520, 1.8, dK / dV: 622 | 798 both; of c = l, n = 15,360, 2.3, dQ:
+//     867 | 1,097;
+//   d = 64, B = 32, two: dQ n = 3,072, 8 heads 4.1: 20 | 22; dK / dV l = 512, n = 8,192, 8 heads
+//     1.3: 132 | 106; n = 3,072, 16 heads 2.5: 54 | 53; l = 256, n = 1,024, 16 heads 2.4: 18 |
+//     19; l = 2 n, 64 heads 14: 98 | 186;
+//   d = 64, B = 16, four: dQ n = 3,072, 8 heads 5.6: 23 | 20; l = 512, n = 2,048, 16 heads 8.9:
+//     19 | 20; dK / dV n = 12,288, 8 heads 3.9: 300 | 210, 16 heads 7.8: 334 | 416;
+//   d = 32, B = 32, four: dK / dV l = 1,024, n = 4,096, 16 heads 3.5: 51 | 36; n = 12,288, 16
+//     heads 4.7: 175 | 192.
+// Walks of a few steps gain less than the sum of the phases costs (l = 128, n = 608, one
+// head of 128: 19.5 | 22).
+constexpr double kWalkSteps = 24.0, kMinPhaseSteps = 8.0;
+inline bool walk_phases(const AttnArgs& a, bool columns) {
+    if (a.pattern != FIXED || a.mode == MODE_A1) return false;
+    const WalkEstimate w = walk_estimate(a);
+    const double work = (w.steps + kWalkSteps * a.nq * a.heads * a.batch) / 256.0;
+    const int row = a.d * a.block;  // elements of a ring stage: phases' workgroups per compute unit
+    const double line = columns ? (row > 2048 ? 1.6 : row > 1024 ? 2.3 : 3.8) : (row > 2048 ? 2.2 : row > 1024 ? 4.0 : 6.6);
+    const double longest = columns ? w.longest_column : w.longest_row;
+    return longest >= kMinPhaseSteps && work <= line * longest;
+}
+
 // The (head, query block, batch) of a row-view workgroup, on the grid
 // (heads, nq, batch).  The dispatcher hands consecutive workgroups to the 8
 // XCDs in turn, so workgroup L (x fastest) runs on XCD L mod 8.  A walk of

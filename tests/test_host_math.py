@@ -53,3 +53,14 @@ def test_one_pass_strided_walks_cover_the_merged_set(tmp_path):
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300,
                          env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_walk_rules_of_the_fixed_pattern(tmp_path):
+    exe = tmp_path / "check_walks"
+    subprocess.run([HIPCC, "-O2", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "paper_1904_10509_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "check_walks.cpp"), "-o", str(exe)], check=True,
+                   capture_output=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300,
+                         env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr

@@ -104,31 +104,12 @@ struct AttnArgs {
 __host__ __device__ inline int band_blocks(const AttnArgs& a) { return (a.l - 1) / a.block + 1; }
 constexpr int kLongBand = 8;  // from here on a band's walks count as long
 
-// Whether a workgroup of the forward or the dQ kernel takes two query blocks (four
-// waves of 32 rows): where both walk the same blocks but for the diagonal's, i.e.
-// the strided band, and in the fixed pattern l-blocks of whole pairs.  A staged
-// tile then serves 128 rows, and in the forward each K / V operand read from LDS
-// feeds 32 rows instead of 16, at three waves per SIMD instead of four (with one
-// query block per workgroup the ring's LDS allowed 2.5, and 32 rows were slower).
-// Fixed n = 65,536, 8 heads: forward 0.712 -> 0.643 ms, dQ 0.736 -> 0.702; n =
-// 12,288, 16 heads: forward 110 -> 104 us; dense limit, n = 12,288, 16 heads:
-// forward 375 -> 343 us, backward 1,070 -> 1,020.  Half as many workgroups of twice
-// the length: kWideGroups of them keep the chip full to the end (1,024: 190 against
-// 189 us; 480, n = 4,096: 20.6 against 25.4), and a short band is over before the
-// wider reads pay (l = 128, 3 blocks: 25.5 against 29.2 us).
-constexpr int64_t kWideGroups = 1024;
-inline bool wide_rows(const AttnArgs& a) {
-    if (a.pattern == STRIDED ? a.walk != WALK_BAND || band_blocks(a) < kLongBand
-                             : a.walk != WALK_LAYOUT || a.l % 128 != 0)
-        return false;
-    return (int64_t)a.batch * a.heads * ((a.nq + 1) / 2) >= kWideGroups;
-}
-
 // Block steps of the fixed pattern's walks, from its sizes alone: every step of a call,
 // and the longest walk of a row block and of a key block.  (Per (batch, head) nq walks;
 // those of far blocks, which hold summary keys, reach half the sequence on average,
 // those inside an l-block half of it.)
 struct WalkEstimate {
+    double far, local;  // blocks of the last row: with summary keys, and of its own l-block
     double steps, longest_row, longest_column;
 };
 inline WalkEstimate walk_estimate(const AttnArgs& a) {
@@ -142,10 +123,56 @@ inline WalkEstimate walk_estimate(const AttnArgs& a) {
     const double local = a1_heads == 0 ? 0.0 : least((a.l - 1) / a.block + 1);
     const double column = far > 0.0 ? nq - (a.l - a.c) / a.block : 0.0;
     WalkEstimate w;
+    w.far = far;
+    w.local = local;
     w.steps = 0.5 * nq * a.batch * (a2_heads * far + a1_heads * (local + 1.0));
     w.longest_row = a.mode == MODE_MERGED ? far + local : far > local ? far : local;
     w.longest_column = column > local ? column : local;
     return w;
+}
+
+// Whether a workgroup of the forward or the dQ kernel takes two query blocks (four
+// waves of 32 rows): where both walk the same blocks but for the diagonal's, i.e.
+// the strided band, and in the fixed pattern l-blocks of whole pairs.  A staged
+// tile then serves 128 rows, and in the forward each K / V operand read from LDS
+// feeds 32 rows instead of 16, at three waves per SIMD instead of four (with one
+// query block per workgroup the ring's LDS allowed 2.5, and 32 rows were slower).
+// Fixed n = 65,536, 8 heads: forward 0.712 -> 0.643 ms, dQ 0.736 -> 0.702; n =
+// 12,288, 16 heads: forward 110 -> 104 us; dense limit, n = 12,288, 16 heads:
+// forward 375 -> 343 us, backward 1,070 -> 1,020.  Half as many workgroups of twice
+// the length: kWideGroups of them keep the chip full to the end (strided band, 1,024:
+// 190 against 189 us; 480, n = 4,096: 20.6 against 25.4), and a short walk is over before
+// the wider reads pay (strided, l = 128, 3 blocks: 25.5 against 29.2 us).  In the fixed
+// pattern rows differ in length, and the line depends on how many steps an average row
+// walks: far ones (summary halves in pairs count once) and those of its own l-block.
+// Forward, us, one block | two, c = 32 unless given:
+//   kWideGroups, 16 far steps: n = 4,096, l = 128, c = 40, 32 heads 74 | 64; fewer: c = 32, 8 far
+//     39 | 42, c = 64, l = 256, 8 far 40 | 43, l = 512 31 | 35;
+//   half as many again (n = 12,288, 16 heads): merged, 6 far: l = 128, 24 131 | 119, l = 512, 6
+//     62 | 61 (dQ 79 | 75), n = 12,224, l = 2,944, 2.5 116 | 128; A2 alone, 3: l = 1,024 26 | 25,
+//     l = 2,048, 1.5 19 | 20; alternating heads, 8: l = 256, 12 59 | 54, l = 512, 6 37 | 41, l =
+//     2,048, 1.5 83 | 98;
+//   twice as many: long walks inside the l-blocks as well, which leave few workgroups to the
+//     end; A1 alone, 12 steps: n = 16,384, 32 heads, l = 2,048 223 | 213, l = 1,024 112 | 118,
+//     l = 128 47 | 51 (with fewer: n = 12,288, 16 heads, l = 2,048 93 | 100, l = 128 21 | 23, dQ
+//     34 | 37); merged, 10: n = 8,192, 32 heads, l = 2,048, 18.5 128 | 119, l = 512, 8.5 66 | 65.
+constexpr int64_t kWideGroups = 1024;
+inline bool wide_rows(const AttnArgs& a) {
+    const int64_t groups = (int64_t)a.batch * a.heads * ((a.nq + 1) / 2);
+    if (a.pattern == STRIDED) return a.walk == WALK_BAND && band_blocks(a) >= kLongBand && groups >= kWideGroups;
+    if (a.walk != WALK_LAYOUT || a.l % 128 != 0 || groups < kWideGroups) return false;
+    const WalkEstimate w = walk_estimate(a);
+    const bool pairs = a.c == 32 && a.block == 64;
+    const double far = (pairs ? 0.25 : 0.5) * w.far, local = 0.5 * (w.local + 1.0);
+    if (far >= 16.0) return true;
+    if (groups < kWideGroups + kWideGroups / 2) return false;
+    const bool many = groups >= 2 * kWideGroups;
+    switch (a.mode) {
+    case MODE_A1: return many && local >= 12.0;
+    case MODE_A2: return far >= 3.0;
+    case MODE_MERGED: return far >= 6.0 || (many && far + local >= 10.0);
+    default: return far >= 8.0;
+    }
 }
 
 // Whether four waves share each row's (dQ) or each key group's (dK / dV) walk, in the

@@ -1,6 +1,7 @@
 // Host check of the dispatch rules on the fixed pattern's walks: the estimate of their
-// block steps and longest walks against a count of the present blocks, and the rule on
-// sharing a walk among four waves at shapes measured on both sides of its line.
+// block steps and longest walks against a count of the present blocks, and the rules on
+// sharing a walk among four waves and on two query blocks per workgroup at shapes
+// measured on both sides of their lines.
 #include <cstdio>
 
 #include "sa_internal.h"
@@ -89,6 +90,28 @@ int main() {
         if (sa::walk_phases(a, false) != s.rows || sa::walk_phases(a, true) != s.columns) {
             std::printf("fail: phases mode %d n %d l %d c %d B %d d %d %d x %d: rows %d columns %d\n", s.mode, s.n, s.l, s.c,
                         s.B, s.d, s.batch, s.heads, sa::walk_phases(a, false), sa::walk_phases(a, true));
+            return 1;
+        }
+        ++checked;
+    }
+    // two query blocks per workgroup: many workgroups of long walks
+    struct Wide {
+        int mode, n, l, c, batch, heads;
+        bool on;
+    };
+    for (const Wide& s : {
+             Wide{sa::MODE_MERGED, 65536, 256, 32, 1, 8, true}, Wide{sa::MODE_MERGED, 12288, 128, 32, 2, 8, true},
+             Wide{sa::MODE_MERGED, 4096, 128, 40, 4, 8, true}, Wide{sa::MODE_INTERLEAVED, 12288, 256, 32, 2, 8, true},
+             Wide{sa::MODE_A2, 12288, 512, 32, 2, 8, true}, Wide{sa::MODE_A1, 16384, 4096, 32, 4, 8, true},
+             Wide{sa::MODE_MERGED, 8192, 2048, 32, 4, 8, true}, Wide{sa::MODE_MERGED, 12224, 2944, 16, 2, 8, false},
+             Wide{sa::MODE_A1, 12288, 2048, 32, 2, 8, false}, Wide{sa::MODE_A1, 12288, 128, 32, 2, 8, false}, Wide{sa::MODE_A1, 12288, 1024, 32, 2, 8, false},
+             Wide{sa::MODE_MERGED, 2048, 128, 32, 8, 8, false}, Wide{sa::MODE_MERGED, 4096, 512, 32, 4, 8, false},
+             Wide{sa::MODE_INTERLEAVED, 12288, 512, 32, 2, 8, false}, Wide{sa::MODE_INTERLEAVED, 12288, 2048, 32, 2, 8, false},
+             Wide{sa::MODE_A2, 12288, 2048, 32, 2, 8, false}, Wide{sa::MODE_A2, 2048, 256, 32, 8, 8, false},
+         }) {
+        const sa::AttnArgs a = call(s.mode, s.n, s.l, s.c, 64, 64, s.batch, s.heads);
+        if (sa::wide_rows(a) != s.on) {
+            std::printf("fail: wide mode %d n %d l %d c %d %d x %d\n", s.mode, s.n, s.l, s.c, s.batch, s.heads);
             return 1;
         }
         ++checked;

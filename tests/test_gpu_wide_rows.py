@@ -1,6 +1,6 @@
-"""Workgroups of two query blocks (taken from 1,024 of them on): an odd number of
-query blocks, one l-block per pair and several, each head mode, the strided
-band and the dense limit, against the fp64 oracle."""
+"""Many query blocks, walked one or, where the walks are long too, two per workgroup
+(see wide_rows): an odd number of query blocks, one l-block per pair and several,
+each head mode, the strided band and the dense limit, against the fp64 oracle."""
 import pytest
 import torch
 
@@ -23,6 +23,11 @@ A1, A2, MG, IL = sa.SA_MODE_A1, sa.SA_MODE_A2, sa.SA_MODE_MERGED, sa.SA_MODE_INT
     (F, IL, 2112, 128, 40, 8, 8),
     (F, A1, 2048, 384, 32, 8, 8),
     (P, MG, 2112, 128, 32, 8, 8),
+    (F, MG, 2112, 128, 96, 8, 8),     # 16 far steps a row on average, 17 x 64 workgroups
+    (F, A2, 2112, 128, 128, 8, 8),
+    (F, IL, 2112, 128, 96, 8, 8),
+    (F, A1, 2112, 2048, 32, 16, 8),   # 17 x 128 workgroups, one long l-block and the start of another
+    (P, MG, 4416, 128, 32, 6, 8),     # summary halves in pairs, 35 x 48 workgroups
     (S, A1, 2112, 500, 0, 8, 8),      # a band of eight blocks and the diagonal one
     (S, MG, 2112, 5000, 0, 8, 8),     # the dense limit
 ])

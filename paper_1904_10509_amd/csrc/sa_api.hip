@@ -278,7 +278,7 @@ bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
                                     : far >= kFarToBand * (sa::band_blocks(s->rows) + 1) &&
                                           far >= (d == 128 ? 6.0 : 4.0) * (p.block == 64 ? 1.0 : p.block == 32 ? 1.6 : 2.5);
         s->fused = better && p.l >= kFusedMinStride && 64 * (int64_t)p.l * strides[2] < ((int64_t)1 << 32) &&
-                   sa::strided_tiles(s->rows) < (1 << 22);
+                   sa::strided_grid_fits(s->rows);
         if (s->fused) return true;
         if (!aligned) return false;
     } else if (p.l % p.block != 0 && 0.5 * (double)M * steps < (alternate ? kMinFarAlternate : kMinFarBlocks)) {

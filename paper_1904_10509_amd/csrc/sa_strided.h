@@ -15,6 +15,11 @@ inline int64_t strided_tiles(const AttnArgs& a) {
     return ((M + 15) / 16) * ((a.l - 1) / 16 + 1) * a.batch * a.heads;
 }
 
+// Workgroups of a launch: the tiles are dealt to the eight XCDs in equal shares (see
+// strided_tile).  The largest has 1,024 threads, and a launch holds fewer than 2^32.
+inline int64_t strided_groups(const AttnArgs& a) { return (strided_tiles(a) + 7) / 8 * 8; }
+inline bool strided_grid_fits(const AttnArgs& a) { return strided_groups(a) * 1024 < ((int64_t)1 << 32); }
+
 // The 16 x 16 tile of a workgroup.
 struct STile {
     int b, h, m0, r0;

@@ -527,13 +527,10 @@ strided_dkdv_kernel(AttnArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     }
 }
 
-// (the tiles are dealt to the eight XCDs in equal shares, see strided_tile)
-unsigned strided_groups(const AttnArgs& a) { return (unsigned)((strided_tiles(a) + 7) / 8 * 8); }
-
 template <int D>
 hipError_t launch_fwd(const AttnArgs& a, const void* q, const void* k, const void* v, void* o, float* lse,
                       hipStream_t stream) {
-    hipLaunchKernelGGL((strided_fwd_kernel<D, 8>), dim3(strided_groups(a)), dim3(512), 0, stream, a,
+    hipLaunchKernelGGL((strided_fwd_kernel<D, 8>), dim3((unsigned)strided_groups(a)), dim3(512), 0, stream, a,
                        (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (uint16_t*)o, lse);
     return hipGetLastError();
 }
@@ -551,12 +548,12 @@ hipError_t launch_bwd(const AttnArgs& a, const void* q, const void* k, const voi
                            0, stream, a, (const uint16_t*)o, (const uint16_t*)dout, lse, ws.ndelta, ws.nlse2,
                            (unsigned long long*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
     if (parts & BWD_DQ)
-        hipLaunchKernelGGL((strided_dq_kernel<D, 8>), dim3(strided_groups(a)), dim3(512), 0, stream, aq,
+        hipLaunchKernelGGL((strided_dq_kernel<D, 8>), dim3((unsigned)strided_groups(a)), dim3(512), 0, stream, aq,
                            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
                            (const uint16_t*)o, lse, ws.nlse2, ws.ndelta, (uint16_t*)dq);
     constexpr int W = D == 128 ? 8 : 16;
     if (parts & BWD_DKDV)
-        hipLaunchKernelGGL((strided_dkdv_kernel<D, W>), dim3(strided_groups(a)), dim3(64 * W), 0, stream, a,
+        hipLaunchKernelGGL((strided_dkdv_kernel<D, W>), dim3((unsigned)strided_groups(a)), dim3(64 * W), 0, stream, a,
                            (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout, ws.nlse2,
                            ws.ndelta, (uint16_t*)dk, (uint16_t*)dv);
     return hipGetLastError();

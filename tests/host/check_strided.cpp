@@ -72,6 +72,17 @@ int main() {
                     if (by_key[(size_t)i * n + j] != want) return fail("keys", n, l);
                 }
         }
+    // a launch holds fewer than 2^32 threads: shares of eight workgroups of up to 1,024
+    for (int tiles = (1 << 22) - 16; tiles <= (1 << 22) + 16; ++tiles) {
+        sa::AttnArgs a{};
+        a.n = 256;
+        a.l = 16;
+        a.batch = 1;
+        a.heads = tiles;
+        if (sa::strided_tiles(a) != tiles) return fail("tiles", a.n, a.l);
+        const int64_t threads = ((int64_t)tiles + 7) / 8 * 8 * 1024;
+        if (sa::strided_grid_fits(a) != (threads < ((int64_t)1 << 32))) return fail("grid", tiles, a.l);
+    }
     std::printf("ok %lld pairs\n", checked);
     return 0;
 }

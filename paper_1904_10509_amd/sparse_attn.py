@@ -109,9 +109,11 @@ def _ptr(t):
 
 
 def _stream(stream, device):
-    if stream is None and device.type == "cuda":  # the handle alone, without a torch.cuda.Stream around it
-        return torch._C._cuda_getCurrentRawStream(device.index)
     if stream is None:
+        # the handle alone, without a torch.cuda.Stream around it, where torch offers it (no public name)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and device.type == "cuda" and device.index is not None:
+            return raw(device.index)
         stream = torch.cuda.current_stream(device)
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 

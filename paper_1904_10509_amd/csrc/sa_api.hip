@@ -117,6 +117,7 @@ sa::AttnArgs make_args(const PatternArgs& p, int32_t batch, int32_t heads, int32
     a.claim_mode = sa::CLAIM_QUEUES;
     a.pairs = 0;
     a.row_stats = 0;
+    a.sched_first = 0;
     a.dl = sa::make_divl(p.l);
     a.walk = sa::WALK_LAYOUT;
     a.qshift = 0;

@@ -394,14 +394,10 @@ bwd_dq_bf16_kernel(AttnArgs a, const int32_t* __restrict__ row_ptr, const int32_
                    int32_t* __restrict__ order) {
     using C = DqCfg<D, BLK, PAT, WIDE, PH>;
     if (a.row_stats && queue) {  // uniform over the workgroup
-        // by the workgroups of the shortest rows where the whole grid runs at
-        // once, else by some in its middle: before one of the longest rows (the
-        // first workgroups) it lengthens the launch, after all others too
         const int64_t wg = blockIdx.x + (int64_t)gridDim.x * (blockIdx.y + (int64_t)gridDim.y * blockIdx.z);
-        const int64_t all = (int64_t)gridDim.x * gridDim.y * gridDim.z;
         const int layouts = layout_count(a.mode, a.sub);
-        const int64_t first = all <= 768 ? all - layouts : (all - layouts) / 2;
-        if (wg >= first && wg < first + layouts) build_schedule(a, (int)(wg - first), queue, items, order);
+        if (wg >= a.sched_first && wg < a.sched_first + layouts)
+            build_schedule(a, (int)(wg - a.sched_first), queue, items, order);
     }
     __shared__ __attribute__((aligned(16))) uint16_t sK[C::NS * PH][BLK * D];
     __shared__ __attribute__((aligned(16))) uint16_t sV[C::NS * PH][BLK * D];
@@ -1623,10 +1619,19 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
             auto dq_launch = [&](auto sp, auto wide, auto ph) {
                 constexpr bool W = decltype(wide)::value;
                 constexpr int PH = decltype(ph)::value;
+                constexpr auto kernel =
+                    bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value, W, PH>;
                 const dim3 g = W ? dim3(grid.x, (grid.y + 1) / 2, grid.z) : grid;
-                hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, BLK, PAT, MODE, decltype(fb)::value, decltype(sp)::value, W,
-                                                       PH>),
-                                   g, dim3(DqCfg<D, BLK, PAT, W, PH>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
+                // The dK / dV schedule is built by the workgroups of the shortest rows
+                // (the last) where the whole grid runs at once, else by some in its
+                // middle: before one of the longest rows it lengthens the launch, after
+                // all others too (statistics and dQ, us, with a line at 768 workgroups |
+                // at the grids that run at once: n = 3,072, B = 64, 18 heads of 64, 864
+                // workgroups 26.5 | 23.0; 4 of 128, B = 32, 384 in four phases 25.2 | 22.1).
+                const int64_t all = (int64_t)g.x * g.y * g.z, rest = all - layout_count(a.mode, a.sub);
+                const bool at_once = sched && all <= resident_workgroups<kernel>(DqCfg<D, BLK, PAT, W, PH>::NT);
+                aq.sched_first = at_once ? rest : rest / 2;
+                hipLaunchKernelGGL(kernel, g, dim3(DqCfg<D, BLK, PAT, W, PH>::NT), 0, stream, aq, a.row_ptr, a.col_idx,
                                    (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)dout,
                                    nlse2, ndelta, (uint16_t*)dq, (const uint16_t*)o, lse, sched, ws.items,
                                    ws.order);

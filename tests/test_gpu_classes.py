@@ -1,6 +1,7 @@
-"""Strided heads by band and residue classes where the classes do not fill
-their blocks (l not dividing n, or n / l not a multiple of the class block), l
-does not fit the block grid, and heads alternate: against the fp64 oracle."""
+"""Strided heads by band and residue classes or in one pass where the classes do not
+fill their blocks (l not dividing n, or n / l not a multiple of the class block), l
+does not fit the block grid, and heads alternate, and the same where B divides l and
+the block path stays: against the fp64 oracle."""
 import pytest
 import torch
 
@@ -23,19 +24,23 @@ CASES = [
     (MG, 1600, 64, 49, 32, 1, 1),     # 32 or 33, one (batch, head)
     (MG, 2048, 16, 31, 64, 1, 2),     # 66 or 67
     (MG, 3072, 64, 24, 64, 1, 2),     # 128 exactly, l < B
-    (MG, 2064, 16, 16, 128, 1, 2),    # 129: past one launch per class
-    (MG, 1552, 16, 12, 128, 1, 1),    # 129 or 130 at d = 128
-    (MG, 1168, 16, 12, 128, 2, 1),    # 97 or 98 at d = 128
-    (MG, 4112, 16, 16, 64, 1, 2),     # 257: class blocks of 64, a last block of one
+    (MG, 2064, 16, 16, 128, 1, 2),    # 129, B divides l: the block path
+    (MG, 1552, 16, 12, 128, 1, 1),    # 129 or 130
+    (MG, 1168, 16, 12, 128, 2, 1),    # 97 or 98
+    (MG, 4112, 16, 16, 64, 1, 2),     # 257, B divides l
     (MG, 2000, 16, 3, 32, 1, 2),      # 666 or 667
-    (MG, 3072, 64, 128, 128, 2, 2),   # 24
-    (MG, 832, 64, 64, 64, 1, 2),      # 13: class blocks of 16
+    (MG, 3072, 64, 128, 128, 2, 2),   # 24, B divides l
+    (MG, 832, 64, 64, 64, 1, 2),      # 13, B divides l
     (MG, 1024, 64, 64, 64, 6, 8),     # 16: 192 workgroups of the one-pass forward, its smallest
     (MG, 1024, 64, 64, 64, 1, 47),    # 188: band and classes apart
     (A2, 1008, 16, 50, 64, 1, 2),     # 20 or 21
     (A2, 1088, 64, 130, 64, 2, 2),    # 8 or 9
     (A2, 2000, 16, 7, 128, 1, 1),     # 285 or 286
-    (IL, 1024, 64, 64, 64, 2, 4),
+    (A2, 2320, 16, 24, 128, 1, 1),    # 96 or 97: past one launch per class at d = 128
+    (A2, 3104, 16, 24, 64, 1, 2),     # 129 or 130: past one launch per class
+    (A2, 6160, 16, 24, 64, 1, 1),     # 256 or 257: class blocks of 64, a last block of one
+    (A2, 2048, 16, 24, 32, 2, 1),     # 85 or 86 in one launch
+    (IL, 1024, 64, 64, 64, 2, 4),     # B divides l: the block path
     (IL, 992, 32, 45, 64, 1, 5),      # an odd number of heads
     (IL, 992, 32, 45, 128, 2, 3),     # odd and batched: the classes' heads make no one index
     (IL, 1280, 64, 30, 32, 1, 1),     # no odd head

@@ -21,8 +21,19 @@ pytestmark = pytest.mark.gpu
     (sa.SA_FIXED, 1, 8, 65536, 256, 32),
 ])
 def test_repeated_calls_same_bits(pattern, batch, heads, n, l, c):
+    repeat(pattern, batch, heads, n, l, c, 64)
+
+
+# the one-pass strided kernels: each wave refills its own LDS tiles by direct loads
+# while it works on what it read from them, and the tiles' space hands the fp32 sums over
+@pytest.mark.parametrize("batch,heads,n,l,d", [(2, 8, 12288, 111, 64), (2, 4, 4096, 60, 128), (4, 8, 2048, 37, 32)])
+def test_repeated_one_pass_calls_same_bits(batch, heads, n, l, d):
+    repeat(sa.SA_STRIDED, batch, heads, n, l, 0, d)
+
+
+def repeat(pattern, batch, heads, n, l, c, d):
     dev = device()
-    x = make_inputs(batch, heads, n, 64, torch.bfloat16, seed=n + l + pattern)
+    x = make_inputs(batch, heads, n, d, torch.bfloat16, seed=n + l + pattern)
     q, k, v, dout = (x[name].to(dev) for name in ("q", "k", "v", "dout"))
     lay = sa.build_layout(n, 64, l, c, pattern, sa.SA_MODE_MERGED, device=dev)
     print(f"determinism pattern={pattern} {batch}x{heads} n={n} l={l} c={c}", flush=True)

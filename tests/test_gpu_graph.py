@@ -13,7 +13,8 @@ from gpu_util import device
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("pattern,n,B,l,c", [(sa.SA_STRIDED, 2048, 64, 128, 0), (sa.SA_FIXED, 2048, 64, 256, 32)])
+@pytest.mark.parametrize("pattern,n,B,l,c", [(sa.SA_STRIDED, 2048, 64, 128, 0), (sa.SA_FIXED, 2048, 64, 256, 32),
+                                             (sa.SA_STRIDED, 2048, 64, 45, 0)])  # 45: the one-pass kernels
 def test_graph_replays_match_eager(pattern, n, B, l, c):
     dev = device()
     x = make_inputs(2, 4, n, 64, torch.bfloat16, seed=n + l)

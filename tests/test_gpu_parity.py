@@ -123,14 +123,14 @@ SMALL_CASES = [
     (P, MG, 1024, 64, 128, 2, 32, torch.bfloat16, 1, 64),
     (P, A2, 512, 16, 64, 8, 32, torch.bfloat16, 1, 8),
     # strided merged and A2 heads with l | n and n / l a multiple of 16 take
-    # A2 by residue classes (the band over the layout, then dense causal
-    # attention inside each class, merged in place): classes of 16, 32, 48,
-    # 64, 96, 128 and 256 positions (class blocks of 16, 32, 16, 32, 32, 32,
+    # A2 by residue classes (the band, walked without the layout, then dense
+    # causal attention inside each class, merged in place; merged forwards from
+    # 192 workgroups on in one pass): classes of 16, 32, 48, 64, 96, 128 and 256
+    # positions (class blocks of 16, 32, 32 with the last one padded, 32, 32, 32,
     # 64), l / B of 1, 2, 4, A2 alone with l < B, d = 32 / 64 / 128, several
-    # (batch, head) pairs.  Classes of 32 to 128 positions (a multiple of 32)
-    # run their backward as one launch per class, except 128 positions at
-    # d = 128 (too large for LDS), which keeps the separate dQ and dK / dV
-    # launches; 16, 48 and 256 positions keep them too.
+    # (batch, head) pairs.  Classes of up to 128 positions run their backward as
+    # one launch per class (96 at d = 128, LDS), longer ones keep the separate dQ
+    # and dK / dV launches.
     (S, MG, 1024, 32, 64, 0, 64, torch.bfloat16, 2, 3),
     (S, MG, 2048, 64, 64, 0, 128, torch.bfloat16, 1, 2),
     (S, MG, 3072, 16, 32, 0, 32, torch.bfloat16, 1, 2),

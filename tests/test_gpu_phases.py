@@ -1,5 +1,5 @@
-"""Fixed pattern with B < 64 and few long columns: four waves share each row's and
-each key group's walk.  Walks shorter than the phases, of every remainder, empty
+"""Fixed pattern with B < 64: while the walks do not fill the chip four waves share
+each row's and each key group's, else they are walked alone.  Walks shorter than the phases, of every remainder, empty
 rows and columns, d = 32 / 64 / 128, with and without two-part products, and the
 same bits on every run; against the fp64 oracle."""
 import pytest
@@ -32,6 +32,23 @@ A2, MG, IL = sa.SA_MODE_A2, sa.SA_MODE_MERGED, sa.SA_MODE_INTERLEAVED
     (F, MG, 1040, 16, 64, 2, 32, 1, 2),
 ])
 def test_shared_walks(pattern, mode, n, B, l, c, d, batch, heads):
+    run(pattern, mode, n, B, l, c, d, batch, heads)
+
+
+# the other side of walk_phases: enough walks to fill the chip, each walked alone
+@pytest.mark.parametrize("pattern,mode,n,B,l,c,d,batch,heads", [
+    (F, MG, 512, 32, 128, 32, 64, 8, 16),
+    (F, A2, 512, 32, 64, 1, 32, 2, 32),     # two-part products
+    (F, IL, 512, 16, 64, 8, 128, 4, 8),     # the same at d = 128
+    (P, MG, 512, 32, 64, 16, 128, 4, 8),
+    (F, MG, 336, 16, 25, 25, 32, 8, 16),
+    (F, MG, 512, 16, 1000, 32, 64, 4, 16),  # one l-block: long walks inside it alone
+])
+def test_walks_alone(pattern, mode, n, B, l, c, d, batch, heads):
+    run(pattern, mode, n, B, l, c, d, batch, heads)
+
+
+def run(pattern, mode, n, B, l, c, d, batch, heads):
     x = make_inputs(batch, heads, n, d, torch.bfloat16, seed=n + l + c + d)
     kw = dict(n=n, block=B, l=l, c=c, pattern=pattern, mode=mode, scale=d ** -0.5)
     got, again = run_gpu(x, **kw, dev=device()), run_gpu(x, **kw)

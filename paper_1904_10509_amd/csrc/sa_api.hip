@@ -93,8 +93,7 @@ int check_tensor_args(const PatternArgs& p, int32_t batch, int32_t heads, int32_
 
 sa::AttnArgs make_args(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
                        const int64_t* strides, float scale, const int32_t* row_ptr,
-                       const int32_t* col_idx, const uint8_t* kind, const int32_t* col_ptr,
-                       const int32_t* row_idx, const uint8_t* kind_t) {
+                       const int32_t* col_idx, const int32_t* col_ptr, const int32_t* row_idx) {
     sa::AttnArgs a;
     a.pattern = p.pattern;
     a.mode = p.mode;
@@ -130,10 +129,8 @@ sa::AttnArgs make_args(const PatternArgs& p, int32_t batch, int32_t heads, int32
     a.seq = 0;
     a.row_ptr = row_ptr;
     a.col_idx = col_idx;
-    a.kind = kind;
     a.col_ptr = col_ptr;
     a.row_idx = row_idx;
-    a.kind_t = kind_t;
     return a;
 }
 
@@ -159,8 +156,7 @@ int class_view(int64_t n, int32_t l, int32_t cb, int32_t shift, int64_t units, i
     if (st != SA_OK) return st;
     st = check_tensor_args(c, (int32_t)units, l, d, dtype, cls_strides);
     if (st != SA_OK) return st;
-    *cls = make_args(c, (int32_t)units, l, d, cls_strides, scale, nullptr, nullptr, nullptr, nullptr, nullptr,
-                     nullptr);
+    *cls = make_args(c, (int32_t)units, l, d, cls_strides, scale, nullptr, nullptr, nullptr, nullptr);
     cls->walk = sa::WALK_DENSE;
     cls->qshift = shift;
     cls->seq = M * l == n ? 0 : (int32_t)n;
@@ -254,7 +250,7 @@ bool strided_plan(const PatternArgs& p, int32_t batch, int32_t heads, int32_t d,
     auto subset = [&](int32_t count, int32_t first) {
         const int64_t step = alternate ? 2 : 1;
         const int64_t st[3] = {strides[0], step * strides[1], strides[2]};
-        sa::AttnArgs a = make_args(pb, batch, count, d, st, scale, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+        sa::AttnArgs a = make_args(pb, batch, count, d, st, scale, nullptr, nullptr, nullptr, nullptr);
         a.walk = sa::WALK_BAND;
         a.lse_sb = (int64_t)heads * p.n;
         a.lse_sh = step * p.n;
@@ -357,8 +353,7 @@ int check_bwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_c, int
         return SA_ERR_INVALID;
     if (!isfinite(softmax_scale) || !(softmax_scale > 0.f)) return SA_ERR_INVALID;
     *need = sa::bwd_workspace_bytes(batch, heads, n, p.nq, p.n_layouts);
-    *a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx, kind, col_ptr, row_idx,
-                   kind_t);
+    *a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx, col_ptr, row_idx);
     *planned = strided_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, true, plan);
     return SA_OK;
 }
@@ -487,8 +482,7 @@ int sparse_attn_fwd(int64_t n, int32_t block, int32_t stride_l, int32_t summary_
     if (!row_ptr || !col_idx || !kind || !q || !k || !v || !o || !lse) return SA_ERR_INVALID;
     if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o)) return SA_ERR_INVALID;
     if (!isfinite(softmax_scale) || !(softmax_scale > 0.f)) return SA_ERR_INVALID;
-    sa::AttnArgs a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx,
-                               kind, nullptr, nullptr, nullptr);
+    sa::AttnArgs a = make_args(p, batch, heads, d_head, strides, softmax_scale, row_ptr, col_idx, nullptr, nullptr);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     StridedPlan plan;
     if (strided_plan(p, batch, heads, d_head, dtype, strides, softmax_scale, false, &plan)) {
@@ -669,7 +663,7 @@ int sparse_attn_fwd_transposed(int64_t n, int32_t block, int32_t stride_l, int32
     const hipStream_t s = static_cast<hipStream_t>(stream);
     // the band (strided A1 layout), then the classes merged into it
     const sa::AttnArgs band = make_args(p.band, batch, heads, d_head, p.strides, softmax_scale, row_ptr, col_idx,
-                                        kind, nullptr, nullptr, nullptr);
+                                        nullptr, nullptr);
     sa::AttnArgs cls = p.cls;
     cls.epilogue = sa::EPI_MERGE;
     hipError_t e = sa::fwd_launch(band, dtype, q, k, v, o, lse, s);
@@ -698,7 +692,7 @@ int sparse_attn_bwd_transposed(int64_t n, int32_t block, int32_t stride_l, int32
     // the band's backward given the merged O and LSE, then the classes' dQ and
     // dK / dV added to it
     const sa::AttnArgs band = make_args(p.band, batch, heads, d_head, p.strides, softmax_scale, row_ptr, col_idx,
-                                        kind, col_ptr, row_idx, kind_t);
+                                        col_ptr, row_idx);
     sa::AttnArgs cls = p.cls;
     cls.epilogue = sa::EPI_ADD;
     hipError_t e = sa::bwd_launch(band, dtype, q, k, v, o, dout, lse, dq, dk, dv, workspace, s);

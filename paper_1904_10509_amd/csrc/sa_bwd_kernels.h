@@ -301,25 +301,20 @@ __device__ void build_schedule(const AttnArgs& a, int g, unsigned long long* que
     if (tid == 0) items_out[g] = items;
 }
 
-// Rows of the row-statistics kernel per 256-thread workgroup: one thread per
-// row in fp32; in bf16 four lanes per row, lane g reading the 16-byte chunks
-// 8 g + 32 ks (ks = 0 .. D/32 - 1), the chunks the dQ kernel's lane g holds, so
-// that D sums in the dQ kernel's order (see bwd_dq_bf16_kernel's row_stats):
-// the same bits whichever kernel computes it.
-template <int D, typename T>
-constexpr int pre_rows_per_group() {
-    return sizeof(T) == 2 ? 64 : 256;
-}
+// Row statistics (bf16; in fp32 the dQ kernel always forms them): four lanes per
+// row, lane g reading the 16-byte chunks 8 g + 32 ks (ks = 0 .. D/32 - 1), the chunks
+// the dQ kernel's lane g holds, so that D sums in the dQ kernel's order (see
+// bwd_dq_bf16_kernel's row_stats): the same bits whichever kernel computes it.
+constexpr int kPreRows = 64;  // per workgroup of 256 threads
 
-template <int D, typename T>
+template <int D>
 __global__ void __launch_bounds__(256)
-bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, const float* __restrict__ lse,
-               float* __restrict__ ndelta, float* __restrict__ nlse2, unsigned long long* __restrict__ queue,
-               int32_t* __restrict__ items, int32_t* __restrict__ order) {
+bwd_pre_kernel(AttnArgs a, const uint16_t* __restrict__ o, const uint16_t* __restrict__ dout,
+               const float* __restrict__ lse, float* __restrict__ ndelta, float* __restrict__ nlse2,
+               unsigned long long* __restrict__ queue, int32_t* __restrict__ items, int32_t* __restrict__ order) {
     if (queue && (int)blockIdx.x < layout_count(a.mode, a.sub)) build_schedule(a, blockIdx.x, queue, items, order);
-    constexpr int kLanes = sizeof(T) == 2 ? 4 : 1;  // lanes per row
-    const int64_t row = (int64_t)blockIdx.x * pre_rows_per_group<D, T>() + threadIdx.x / kLanes;
-    const int g = threadIdx.x % kLanes;
+    const int64_t row = (int64_t)blockIdx.x * kPreRows + threadIdx.x / 4;
+    const int g = threadIdx.x % 4;
     const int64_t rows = (int64_t)a.batch * a.heads * a.n;
     // (the four lanes of a row share their wave and its exit, so every lane
     // of a row reaches the reduction below)
@@ -328,15 +323,11 @@ bwd_pre_kernel(AttnArgs a, const T* __restrict__ o, const T* __restrict__ dout, 
     const int b = (int)(bh / a.heads), h = (int)(bh % a.heads);
     const int64_t off = head_base(a, b, h) + i * a.ss, si = stat_index(a, b, h, i);
     float acc = 0.f;
-    if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks)
-            acc += dot_bf16x8(ld_bf16x8(dout + off + ks * 32 + 8 * g), ld_bf16x8(o + off + ks * 32 + 8 * g));
-        acc += __shfl_xor(acc, 1);  // (g0 + g1) and (g2 + g3), then their sum
-        acc += __shfl_xor(acc, 2);
-    } else {
-        for (int t = 0; t < D; ++t) acc = fmaf(o[off + t], dout[off + t], acc);
-    }
+    for (int ks = 0; ks < D / 32; ++ks)
+        acc += dot_bf16x8(ld_bf16x8(dout + off + ks * 32 + 8 * g), ld_bf16x8(o + off + ks * 32 + 8 * g));
+    acc += __shfl_xor(acc, 1);  // (g0 + g1) and (g2 + g3), then their sum
+    acc += __shfl_xor(acc, 2);
     if (g != 0) return;
     ndelta[si] = -acc;
     nlse2[si] = -lse[si] * kLog2e;  // an empty row (LSE = -inf) gives +inf; its items are all masked
@@ -1551,7 +1542,6 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
     const int64_t rows = (int64_t)a.batch * a.heads * a.n;
     float* ndelta = ws.ndelta;
     float* nlse2 = ws.nlse2;
-    constexpr int kPreRows = pre_rows_per_group<D, uint16_t>();
     const int64_t pre_groups = (rows + kPreRows - 1) / kPreRows > layout_count(a.mode, a.sub)
                                    ? (rows + kPreRows - 1) / kPreRows
                                    : layout_count(a.mode, a.sub);
@@ -1612,7 +1602,7 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, const void* q, const void* k, cons
         // (a walk without a layout takes its columns in order: no schedule)
         unsigned long long* const sched = a.walk == WALK_LAYOUT ? ws.queue : nullptr;
         if ((parts & BWD_PRE) && !aq.row_stats)
-            hipLaunchKernelGGL((bwd_pre_kernel<D, uint16_t>), dim3((unsigned)pre_groups), dim3(256), 0, stream, ak,
+            hipLaunchKernelGGL((bwd_pre_kernel<D>), dim3((unsigned)pre_groups), dim3(256), 0, stream, ak,
                                (const uint16_t*)o, (const uint16_t*)dout, lse, ndelta, nlse2, sched, ws.items,
                                ws.order);
         if (parts & BWD_DQ) (void)with_full_body<PAT>(a, [&](auto fb) {

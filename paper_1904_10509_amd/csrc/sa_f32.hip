@@ -659,12 +659,8 @@ hipError_t launch_bwd(const AttnArgs& a, const void* q, const void* k, const voi
                       const float* lse, void* dq, void* dk, void* dv, const BwdWorkspace& ws, hipStream_t stream,
                       int parts) {
     AttnArgs aq = a;
-    aq.row_stats = (parts & BWD_PRE) && (parts & BWD_DQ);  // the dQ grid covers every row
-    const int64_t rows = (int64_t)a.batch * a.heads * a.n;
-    if ((parts & BWD_PRE) && !aq.row_stats)
-        hipLaunchKernelGGL((bwd_pre_kernel<D, float>), dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, a,
-                           (const float*)o, (const float*)dout, lse, ws.ndelta, ws.nlse2,
-                           (unsigned long long*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
+    // the statistics always go with dQ (no call has them alone in fp32); its grid covers every row
+    aq.row_stats = (parts & BWD_PRE) != 0;
     if (parts & BWD_DQ)
         hipLaunchKernelGGL((bwd_dq_f32_kernel<D>), strip_grid(a), dim3(kF32Threads), 0, stream, aq, a.row_ptr,
                            a.col_idx, (const float*)q, (const float*)k, (const float*)v, (const float*)o,

@@ -95,10 +95,8 @@ struct AttnArgs {
                            // ceil((seq - h) / l) of them, the rest of its last block is padding); else 0
     const int32_t* row_ptr;
     const int32_t* col_idx;
-    const uint8_t* kind;
     const int32_t* col_ptr;
     const int32_t* row_idx;
-    const uint8_t* kind_t;
 };
 
 // Blocks before (row) or after (column) the diagonal one in the strided band.

@@ -14,9 +14,10 @@
 // read every tensor twice.
 //
 // A wave walks its unit's other side in chunks of 32 rows (of neighbouring rows
-// in the band, l rows apart in a class), alone: no two units of a phase share
-// them, so nothing is gained by workgroup-wide tiles, and there is no barrier
-// inside a phase.  A chunk goes to the wave's own part of LDS by direct loads,
+// in the band, l rows apart in a class), alone, and there is no barrier inside a
+// phase.  In the class phase no two units share rows.  In the band phase they do
+// (units l rows apart; neighbouring tiles), and each reads its own: where the band
+// kernel's tiles of 64 rows serve a longer band, that is what the one-pass form loses.  A chunk goes to the wave's own part of LDS by direct loads,
 // whole rows at a time (as row operands straight into registers, 16 rows' 16
 // bytes per 16 lanes, the same rows took 52 cycles per KiB and CU: forward at n =
 // 12,288, l = 128 93 us).  Both its forms, by rows and transposed, are read into
@@ -49,8 +50,8 @@ struct SCfg {
     static constexpr int DB = D / 16;
     static constexpr int TILE = 32 * D;  // elements of a staged chunk
     // Exchange of a unit's rows: element d of (unit u, row t) at u XA + t XB + d.
-    // Both strides are 4 modulo 64 words: writing a unit's rows and reading one
-    // row of every unit are free of bank conflicts.
+    // Both strides are odd multiples of 4 words (of 64 banks): writing a unit's rows
+    // and reading one row of every unit are free of bank conflicts.
     static constexpr int XB = D + 4;
     static constexpr int XA = 16 * XB + 4;
 };
@@ -542,9 +543,8 @@ hipError_t launch_bwd(const AttnArgs& a, const void* q, const void* k, const voi
     AttnArgs aq = a;
     aq.row_stats = (parts & BWD_PRE) && (parts & BWD_DQ);  // the dQ grid covers every row
     const int64_t rows = (int64_t)a.batch * a.heads * a.n;
-    constexpr int kPreRows = pre_rows_per_group<D, uint16_t>();
     if ((parts & BWD_PRE) && !aq.row_stats)
-        hipLaunchKernelGGL((bwd_pre_kernel<D, uint16_t>), dim3((unsigned)((rows + kPreRows - 1) / kPreRows)), dim3(256),
+        hipLaunchKernelGGL((bwd_pre_kernel<D>), dim3((unsigned)((rows + kPreRows - 1) / kPreRows)), dim3(256),
                            0, stream, a, (const uint16_t*)o, (const uint16_t*)dout, lse, ws.ndelta, ws.nlse2,
                            (unsigned long long*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
     if (parts & BWD_DQ)

@@ -70,15 +70,18 @@ __device__ inline const void* uniform_ptr(const void* p) {
 }
 
 // One direct-to-LDS load per lane: 16 (or 4) bytes from sbase + voff (sbase
-// wave-uniform, voff a 32-bit byte offset) into the LDS window lds_window.
+// wave-uniform, voff a 32-bit byte offset) into the LDS window lds_window, which
+// goes through m0.  The compiler adds no wait states inside or before such a block, so
+// the block holds those the load may need: one after the write of m0, and five after a
+// vector instruction (a lane read, also one that restores a spilled value) wrote sbase.
 __device__ inline void dma_b128(const void* sbase, uint32_t voff, uint32_t lds_window) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_window)
-                 : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
+                 : : "v"(voff), "s"(sbase), "s"(lds_window) : "memory");
 }
 
 __device__ inline void dma_b32(const void* sbase, uint32_t voff, uint32_t lds_window) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" : : "v"(voff), "s"(sbase), "s"(lds_window)
-                 : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dword %0, %1"
+                 : : "v"(voff), "s"(sbase), "s"(lds_window) : "memory");
 }
 
 // Issues the direct-to-LDS loads of one BLK x D tile (rows 0..BLK-1 at row

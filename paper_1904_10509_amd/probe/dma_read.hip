@@ -25,7 +25,9 @@ __global__ void __launch_bounds__(256) dma_read_kernel(const uint8_t* __restrict
         const void* sp = (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
         const uint32_t voff = 16u * (uint32_t)lane;
         const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds);
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(sp), "s"(m0) : "memory");
+        // the wait states the load needs: one after the write of m0, five after the lane reads
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
+                     : : "v"(voff), "s"(sp), "s"(m0) : "memory");
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         acc ^= win[w][lane * 4];
         __builtin_amdgcn_wave_barrier();  // every lane has read the window before the next load overwrites it

@@ -74,6 +74,8 @@ __device__ inline const void* uniform_ptr(const void* p) {
 // goes through m0.  The compiler adds no wait states inside or before such a block, so
 // the block holds those the load may need: one after the write of m0, and five after a
 // vector instruction (a lane read, also one that restores a spilled value) wrote sbase.
+// The four cycles a load cost 1% (forward + backward, strided n = 12,288, l = 128, 16
+// heads: 178 -> 181 us against a single wait state; fixed n = 65,536 2.63 -> 2.64 ms).
 __device__ inline void dma_b128(const void* sbase, uint32_t voff, uint32_t lds_window) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                  : : "v"(voff), "s"(sbase), "s"(lds_window) : "memory");
